@@ -209,6 +209,7 @@ net_status simfit(const net_obs_desc* o, const net_simfit_opts* opts, float* out
     in.K = K;
     in.n_ref = o->n_ref;
     in.P = P;
+    for (int64_t j = 0; j < n; ++j) in.max_row = std::max(in.max_row, row[j + 1] - row[j]);
     in.t_end = t_end;
     in.frame_num = o->frame_num;
     in.frame_den = o->frame_den;

@@ -388,6 +388,7 @@ struct FitInputs {
     const float* w_src;         // device [n]: assumed weight of the edges out of each vertex
     int32_t n, nf, K, n_ref;
     int64_t P, t_end, frame_num, frame_den;
+    int64_t max_row;            // most candidate pairs of one target
     float rho, offset, inv_jump, sigma, gamma;
     double decay, v_rest, v_reset, v_th, drive_amp;   // the fit's vertex model runs in FP64
     double dt, tau_c, gain;
