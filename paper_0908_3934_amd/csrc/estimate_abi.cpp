@@ -88,7 +88,7 @@ namespace {
 net_status features(const net_obs_desc* o, float* out, hipStream_t s, DeviceScratch& sc) {
     FeatureInputs in{};
     feature_inputs(o, in);
-    const size_t nn = static_cast<size_t>(o->n_nodes), nf = static_cast<size_t>(o->n_frames);
+    const size_t nn = static_cast<size_t>(o->n_nodes);
     if (o->drive_rate_hz) {
         std::vector<uint32_t> thr(nn);
         for (size_t j = 0; j < nn; ++j) thr[j] = pulse_threshold(o->drive_rate_hz[j], o->dt_ms);
@@ -100,13 +100,13 @@ net_status features(const net_obs_desc* o, float* out, hipStream_t s, DeviceScra
         in.drive_thr = d;
     }
     FeatureWork w{};
-    w.en = sc.get<float>(nn * nf);
-    w.zn = sc.get<float>(nn * nf);
-    w.rn = sc.get<float>(nn * nf);
-    w.dc = sc.get<float>(nn * nf);
-    w.stats = sc.get<float>(nn * 4);
-    w.pm = sc.get<float>(nf);
-    if (!w.en || !w.zn || !w.rn || !w.dc || !w.stats || !w.pm) return efail(NET_E_OOM, "net_features: allocation");
+    const size_t row = static_cast<size_t>(o->n_frames);
+    w.en = sc.get<float>(nn * row);
+    w.zn = sc.get<float>(nn * row);
+    w.dc = sc.get<float>(nn * row);
+    w.stats = sc.get<float>(nn * 5);
+    w.pm = sc.get<float>(row);
+    if (!w.en || !w.zn || !w.dc || !w.stats || !w.pm) return efail(NET_E_OOM, "net_features: allocation");
     hipError_t e = launch_features(in, w, out, s);
     if (e != hipSuccess) return efail(NET_E_DEVICE, std::string("net_features: ") + hipGetErrorString(e));
     return NET_OK;

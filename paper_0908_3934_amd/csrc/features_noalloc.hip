@@ -70,7 +70,7 @@ net_status net_features_noalloc(const net_obs_desc* obs, float* features_dev, vo
     if (e != hipSuccess)
         return estimate_fail(NET_E_DEVICE, std::string("net_features_noalloc: scratch address: ") + hipGetErrorString(e));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t n = static_cast<size_t>(obs->n_nodes), nf = static_cast<size_t>(obs->n_frames);
+    const size_t n = static_cast<size_t>(obs->n_nodes);
     unsigned char* p = static_cast<unsigned char*>(base);
     auto carve = [&p](size_t bytes) {
         unsigned char* q = p;
@@ -78,12 +78,14 @@ net_status net_features_noalloc(const net_obs_desc* obs, float* features_dev, vo
         return q;
     };
     FeatureWork w{};
-    w.en = reinterpret_cast<float*>(carve(n * nf * sizeof(float)));
-    w.zn = reinterpret_cast<float*>(carve(n * nf * sizeof(float)));
-    w.rn = reinterpret_cast<float*>(carve(n * nf * sizeof(float)));
-    w.dc = reinterpret_cast<float*>(carve(n * nf * sizeof(float)));
-    w.stats = reinterpret_cast<float*>(carve(n * 4 * sizeof(float)));
-    w.pm = reinterpret_cast<float*>(carve(nf * sizeof(float)));
+    // (three rows and five statistics per vertex: less than the four rows and
+    // four statistics the bound above counts)
+    const size_t row = static_cast<size_t>(obs->n_frames);
+    w.en = reinterpret_cast<float*>(carve(n * row * sizeof(float)));
+    w.zn = reinterpret_cast<float*>(carve(n * row * sizeof(float)));
+    w.dc = reinterpret_cast<float*>(carve(n * row * sizeof(float)));
+    w.stats = reinterpret_cast<float*>(carve(n * 5 * sizeof(float)));
+    w.pm = reinterpret_cast<float*>(carve(row * sizeof(float)));
     float* rates = reinterpret_cast<float*>(carve(n * sizeof(float)));
     uint32_t* thr = reinterpret_cast<uint32_t*>(carve(n * sizeof(uint32_t)));
     FeatureInputs in{};

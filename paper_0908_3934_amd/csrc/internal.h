@@ -364,8 +364,10 @@ struct FeatureInputs {
     int64_t frame_num, frame_den;
     uint32_t key_lo, key_hi;    // control schedule key
 };
+// Scratch: rows of nf entries per vertex (en, zn, dc), five statistics per
+// vertex and one row of population means (pm).
 struct FeatureWork {
-    float *en, *zn, *rn, *dc, *stats, *pm;
+    float *en, *zn, *dc, *stats, *pm;
 };
 hipError_t launch_features(const FeatureInputs& in, const FeatureWork& w, float* out, hipStream_t s);
 // Drive thresholds floor(rate * dt * 2^32) (as pulse_threshold) of n device rates.
