@@ -1,5 +1,6 @@
 // C-ABI entry points of the geonet library (declared in include/geonet.h).
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -259,6 +260,169 @@ bool load_plan(net* h, const HostGraph& hg, int n_cu, int per_cu, int threads, b
     return enable_ensemble_lds(lds_max) == hipSuccess;
 }
 
+// Push ensemble kernel: its launch shape for at most `threads` threads per
+// workgroup.  Returns false where some network has more vertices than the
+// workgroup's registers hold.
+bool shape_push(net* h, int models, int threads, int groups_max, size_t lds_bytes) {
+    const int cap = models > 0 ? kPushThreadsFp64 : kPushThreads;
+    const int waves = std::max(1, std::min(std::min(threads, cap) / 64, groups_max));
+    int vpt = 1;
+    while (vpt * waves < groups_max) vpt *= 2;
+    if (vpt > (models > 0 ? kPushMaxVptFp64 : kPushMaxVpt) || enable_push_ensemble(models, vpt, lds_bytes) != hipSuccess) return false;
+    h->plan.threads = waves * 64;
+    h->plan.vpt = vpt;
+    return true;
+}
+
+// Tables and LDS layout of the push ensemble kernel; false (and nothing
+// uploaded) where a network fits neither its registers nor its LDS.  *st is
+// set when an upload failed.
+bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max, hipStream_t s, int* groups_max, size_t* lds_need,
+               net_status* st) {
+    const int n_nets = h->g.n_nets;
+    const int cap = models > 0 ? kPushThreadsFp64 * kPushMaxVptFp64 : kPushThreads * kPushMaxVpt;
+    const size_t room = std::min<size_t>(lds_max, 152 * 1024);
+    std::vector<PushNet> nets(n_nets);
+    std::vector<int64_t> cost(n_nets);
+    int64_t off_len = 0, ring_len = 0, hist_len = 0;
+    *groups_max = 1;
+    *lds_need = 0;
+    for (int m = 0; m < n_nets; ++m) {
+        PushNet& pn = nets[m];
+        const int64_t n = hg.node_off[m + 1] - hg.node_off[m];
+        if (n > cap) return false;
+        pn.net = m;
+        pn.node_off = static_cast<int32_t>(hg.node_off[m]);
+        pn.n = static_cast<int32_t>(n);
+        pn.groups = static_cast<int32_t>((n + 63) / 64);
+        pn.tbits = 1;
+        while ((int64_t(1) << pn.tbits) < n) ++pn.tbits;
+        // The widest window that LDS and the edge word have room for: each
+        // further window of the delays is one more visit per spike.
+        size_t need = 0;
+        int W = std::min(hg.net_max_delay[m], 1 << (16 - pn.tbits));
+        for (; W >= 1; --W) {
+            const int nw = (hg.net_max_delay[m] + W - 1) / W;
+            const size_t ring = static_cast<size_t>(W + 1) * pn.groups * 64 * sizeof(float);
+            pn.hist_off = static_cast<int32_t>(ring);
+            pn.window = W;
+            pn.n_win = nw;
+            need = ring + (static_cast<size_t>(nw - 1) * W + 2) * pn.groups * 8 + 2 * 33 * sizeof(double);
+            if (need <= room) break;
+        }
+        if (W < 1) return false;
+        pn.off_at = off_len;
+        pn.ring_at = ring_len;
+        pn.hist_at = hist_len;
+        off_len += n * pn.n_win + 1;
+        ring_len += static_cast<int64_t>(pn.window + 1) * pn.groups * 64;
+        hist_len += (static_cast<int64_t>(pn.n_win - 1) * pn.window + 2) * pn.groups;
+        *groups_max = std::max(*groups_max, pn.groups);
+        *lds_need = std::max(*lds_need, need);
+        cost[m] = (hg.net_chunk_end[m] - hg.net_chunk_begin[m]) * kChunkEdges + 8 * n;
+    }
+    // out-edges of every source by window (zero weights, the empty rows'
+    // placeholders among them, add nothing and are left out)
+    std::vector<uint32_t> off(static_cast<size_t>(off_len)), edge;
+    int64_t total = 0;
+    for (int m = 0; m < n_nets; ++m) {
+        const PushNet& pn = nets[m];
+        const int64_t s0 = hg.net_chunk_begin[m] * kChunkEdges, s1 = hg.net_chunk_end[m] * kChunkEdges;
+        uint32_t* o = off.data() + pn.off_at;
+        const int64_t groups = static_cast<int64_t>(pn.n) * pn.n_win;
+        auto group = [&](int64_t k) {
+            return static_cast<int64_t>(hg.src[k] - pn.node_off) * pn.n_win + (hg.d[k] - 1) / pn.window;
+        };
+        for (int64_t k = s0; k < s1; ++k)
+            if ((hg.w[k] & 0x7FFFu) != 0) ++o[group(k)];
+        for (int64_t i = 0; i <= groups; ++i) {
+            const int64_t c = i < groups ? o[i] : 0;
+            if (total > (int64_t(1) << 32) - 1) return false;
+            o[i] = static_cast<uint32_t>(total);
+            total += c;
+        }
+        edge.resize(static_cast<size_t>(total));
+        std::vector<uint32_t> fill(o, o + groups);
+        for (int64_t c = hg.net_chunk_begin[m]; c < hg.net_chunk_end[m]; ++c) {
+            int32_t r = hg.chunk_row0[c];          // the row of a slot: the chunk's first plus the row starts after it
+            for (int64_t k = c * kChunkEdges; k < (c + 1) * kChunkEdges; ++k) {
+                if (k != c * kChunkEdges && ((hg.rowstart[k >> 3] >> (k & 7)) & 1u)) ++r;
+                if ((hg.w[k] & 0x7FFFu) != 0)
+                    edge[fill[group(k)]++] = static_cast<uint32_t>(r - pn.node_off) |
+                                             (static_cast<uint32_t>((hg.d[k] - 1) % pn.window) << pn.tbits) |
+                                             (static_cast<uint32_t>(hg.w[k]) << 16);
+            }
+        }
+    }
+    for (int m = 0; m < n_nets; ++m) {
+        // The unit of the slots' integers: the smallest FP16 spacing among the
+        // network's weights, where every row's sum of magnitudes fits 31 bits
+        // of it (spacing of a value with exponent bits e: 2^(max(e, 1) - 25)).
+        PushNet& pn = nets[m];
+        int lg = 16;
+        for (int64_t k = hg.net_chunk_begin[m] * kChunkEdges; k < hg.net_chunk_end[m] * kChunkEdges; ++k)
+            if ((hg.w[k] & 0x7FFFu) != 0) lg = std::min(lg, std::max((hg.w[k] >> 10) & 31, 1) - 25);
+        int64_t sum = 0, most = 0;
+        for (int64_t c = hg.net_chunk_begin[m]; c < hg.net_chunk_end[m]; ++c)
+            for (int64_t k = c * kChunkEdges; k < (c + 1) * kChunkEdges; ++k) {
+                if ((hg.rowstart[k >> 3] >> (k & 7)) & 1u) sum = 0;
+                const int e = (hg.w[k] >> 10) & 31;
+                const int64_t mant = (hg.w[k] & 0x3FF) | (e ? 0x400 : 0);
+                if (mant != 0) sum += mant << (std::max(e, 1) - 25 - lg);
+                most = std::max(most, sum);
+            }
+        const bool fits = most < (int64_t(1) << 31);
+        pn.unit = fits ? std::ldexp(1.0f, lg) : 0.0f;
+        pn.inv_unit = fits ? std::ldexp(1.0f, -lg) : 0.0f;
+    }
+    if (edge.empty()) edge.push_back(0u);
+    // the costliest networks first: the workgroups that start last are short
+    std::stable_sort(nets.begin(), nets.end(), [&](const PushNet& x, const PushNet& y) { return cost[x.net] > cost[y.net]; });
+    EnsemblePlan& pl = h->plan;
+    // noise drawn ahead (see kNoiseMaxVertices)
+    std::vector<int32_t> noise_nets;
+    bool noisy = false;
+    for (int i = 0; i < n_nets; ++i) {
+        nets[i].noise_at = static_cast<int32_t>(noise_nets.size()) * 64;
+        nets[i].pad = 0;
+        noisy |= hg.params[nets[i].net].sigma != 0.0f;
+        noise_nets.insert(noise_nets.end(), nets[i].groups, i);
+    }
+    const int64_t stride = static_cast<int64_t>(noise_nets.size()) * 64;
+    if (noisy && 2 * n_nets <= n_cu && stride <= kNoiseMaxVertices) {
+        const int32_t steps = static_cast<int32_t>(std::min<int64_t>(1024, kNoiseBytes / (stride * 8)));
+        int32_t* dnn = nullptr;
+        *st = upload(h, &dnn, noise_nets, noise_nets.size(), s, "ensemble plan");
+        if (*st == NET_OK) *st = zeros(h, &pl.noise, static_cast<size_t>(steps * stride), s, "noise");
+        if (*st == NET_OK) *st = zeros(h, &pl.noise_pulses, static_cast<size_t>(steps * (stride / 64)), s, "noise");
+        if (*st != NET_OK) return false;
+        pl.noise_nets = dnn;
+        pl.noise_stride = stride;
+        pl.noise_steps = steps;
+    }
+    PushNet* dn = nullptr;
+    uint32_t *dof = nullptr, *ded = nullptr;
+    *st = upload(h, &dn, nets, nets.size(), s, "ensemble plan");
+    if (*st == NET_OK) *st = upload(h, &dof, off, off.size(), s, "out-edge tables");
+    if (*st == NET_OK) *st = upload(h, &ded, edge, edge.size(), s, "out-edge tables");
+    if (*st == NET_OK) *st = zeros(h, &pl.push_ring, static_cast<size_t>(ring_len), s, "input slots");
+    if (*st == NET_OK) *st = zeros(h, &pl.push_hist, static_cast<size_t>(hist_len), s, "spike bits");
+    if (*st == NET_OK) {
+        const hipError_t e = hipStreamSynchronize(s);   // the host tables are freed below
+        if (e != hipSuccess) *st = device_fail(h, e, "net_build: upload");
+    }
+    if (*st != NET_OK) return false;
+    pl.push_nets = dn;
+    pl.push_off = dof;
+    pl.push_edge = ded;
+    pl.push_ring_bytes = static_cast<size_t>(ring_len) * sizeof(float);
+    pl.push_hist_bytes = static_cast<size_t>(hist_len) * sizeof(uint64_t);
+    pl.push = true;
+    pl.blocks = n_nets;
+    pl.lds_bytes = *lds_need;
+    return true;
+}
+
 // Graph replays: the executable graph of a captured launch sequence.
 // `body` enqueues the launches on the capture stream; the counter is then
 // advanced by `advance` steps inside the graph.
@@ -430,6 +594,8 @@ net_status reset_state(net* h, const HostGraph& hg, hipStream_t s) {
     if (e == hipSuccess) e = hipMemsetAsync(g.I, 0, np * sizeof(float), s);
     if (e == hipSuccess) e = hipMemsetAsync(g.ring, 0, np * kRingWords * sizeof(uint32_t), s);
     if (e == hipSuccess) e = hipMemsetAsync(g.summary, 0, np / 32 * sizeof(uint32_t), s);
+    if (e == hipSuccess && h->plan.push_ring) e = hipMemsetAsync(h->plan.push_ring, 0, h->plan.push_ring_bytes, s);
+    if (e == hipSuccess && h->plan.push_hist) e = hipMemsetAsync(h->plan.push_hist, 0, h->plan.push_hist_bytes, s);
     if (e == hipSuccess && g.age_alt) e = hipMemsetAsync(g.age_alt, kAgeNever, (np + kAgePad) * sizeof(uint16_t), s);
     if (e == hipSuccess && g.summary_alt) e = hipMemsetAsync(g.summary_alt, 0, np / 32 * sizeof(uint32_t), s);
     if (e == hipSuccess && g.calcium) e = hipMemsetAsync(g.calcium, 0, np * sizeof(double), s);
@@ -795,14 +961,82 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
     const bool autotune = (flags & NET_BUILD_AUTOTUNE) != 0;
     const bool single = !push && (n_nets > 1 || (flags & NET_BUILD_SINGLE_LAUNCH));
     if (single && !(flags & NET_BUILD_PER_STEP)) {
+        // whether a source within its network and a delay fit in 16 bits together
+        int64_t max_n = 1;
+        for (int m = 0; m < n_nets; ++m) max_n = std::max(max_n, hg.node_off[m + 1] - hg.node_off[m]);
+        int sb = 1;
+        while ((int64_t(1) << sb) < max_n) ++sb;
+        g.ens_sbits = sb >= 16 || int64_t(hg.max_delay) >= (int64_t(1) << (16 - sb)) ? 16 : sb;
+        // the push ensemble kernel where every network fits its registers and LDS
+        const int models = hg.any_hh ? 2 : (hg.any_izh ? 1 : 0);
+        int dev = 0, n_cu = 0, lds_max = 0, groups_max = 1;
+        size_t lds_need = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+            hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
+            plan_push(h, hg, models, n_cu, static_cast<size_t>(lds_max), s, &groups_max, &lds_need, &st)) {
+            const bool observe = frame_cap > 0 && hg.frame_num > 0;
+            const int opt_thr = opts ? opts->block_threads : 0;
+            const int most = models > 0 ? kPushThreadsFp64 : kPushThreads;
+            std::vector<int> shapes{opt_thr ? opt_thr : most};
+            uint64_t tune_key = 0;
+            bool cached = false;
+            if (autotune && !opt_thr) {
+                for (int t = most / 2; t >= 256; t /= 2) shapes.push_back(t);
+                tune_key = ensemble_fingerprint(hg, descs, n_nets, n_cu, observe);
+                std::lock_guard<std::mutex> lock(g_tune_mutex);
+                for (const auto& c : g_tune_cache)
+                    if (c.first == tune_key) {
+                        shapes = {c.second.second};       // tuned before in this process
+                        cached = true;
+                    }
+            }
+            EnsemblePlan& pl = h->plan;
+            int best = -1;
+            double best_ms = 0.0;
+            for (size_t k = 0; k < shapes.size(); ++k) {
+                if (!shape_push(h, models, shapes[k], groups_max, lds_need)) continue;
+                if (shapes.size() == 1) {
+                    best = 0;
+                    break;
+                }
+                pl.enabled = true;
+                double ms = 0.0;
+                const bool ok = trial_ms(h, 0, 200, s, &ms) && trial_ms(h, 200, 200, s, &ms);
+                pl.enabled = false;
+                if ((st = reset_state(h, hg, s)) != NET_OK) return bail(st);
+                if (!ok) {
+                    (void)hipGetLastError();
+                    continue;
+                }
+                if (best < 0 || ms < best_ms) {
+                    best = static_cast<int>(k);
+                    best_ms = ms;
+                }
+            }
+            // (an explicit shape too small for the largest network: the widest one)
+            if (best < 0) shapes.assign(1, most);
+            pl.enabled = shape_push(h, models, shapes[best < 0 ? 0 : best], groups_max, lds_need);
+            if (!pl.enabled) {
+                device_fail(h, hipErrorUnknown, "net_build: ensemble plan");
+                return bail(NET_E_DEVICE);
+            }
+            h->autotuned = autotune && (shapes.size() > 1 || cached);
+            if (autotune && !cached && shapes.size() > 1) {
+                std::lock_guard<std::mutex> lock(g_tune_mutex);
+                if (g_tune_cache.size() >= 64) g_tune_cache.erase(g_tune_cache.begin());
+                g_tune_cache.push_back({tune_key, {1, shapes[best]}});
+            }
+        }
+        if (st != NET_OK) return bail(st);
+    }
+    if (single && !(flags & NET_BUILD_PER_STEP) && !h->plan.enabled) {
         // the single-launch kernel's 2-byte stream: sources within their
         // network, packed with the delay when both fit in 16 bits
         int64_t max_n = 1;
         for (int m = 0; m < n_nets; ++m) max_n = std::max(max_n, hg.node_off[m + 1] - hg.node_off[m]);
         if (max_n <= 65536) {
-            int sb = 1;
-            while ((int64_t(1) << sb) < max_n) ++sb;
-            if (sb >= 16 || int64_t(hg.max_delay) >= (int64_t(1) << (16 - sb))) sb = 16;
+            const int sb = g.ens_sbits;
             std::vector<uint16_t> ls(static_cast<size_t>(hg.e_slots), 0);
             for (int m = 0; m < n_nets; ++m) {
                 const int64_t off = hg.node_off[m];
@@ -819,7 +1053,6 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
             }
             if (st != NET_OK) return bail(st);
             g.ens_ls = dls;
-            g.ens_sbits = sb;
         }
         // the driven vertices of every network (index within the network, the
         // caller's index for the Philox counter, the rate threshold): noise-free

@@ -92,6 +92,26 @@ inline int ens_log_cap(int64_t n) {
 }
 inline size_t ens_log_bytes(int cap) { return cap > 0 ? 128 + 64 * static_cast<size_t>(cap) : 0; }
 
+// Per-network description used by the push ensemble kernel (one workgroup per
+// network): a ring of window + 1 input slots of 64 x groups words in LDS, then the spike
+// bits of the last (n_win - 1) x window steps, this one and the next, one
+// 64-bit word per step and group of 64 vertices, then two 33-entry calcium
+// tables.
+struct PushNet {
+    int32_t net, node_off, n, groups;
+    int32_t window, n_win;    // delays per window, windows that cover the largest delay
+    int32_t tbits;            // bits of a target in an edge word
+    int32_t hist_off;         // byte offset of the spike bits in LDS
+    int64_t off_at;           // first entry of the network's edge offsets
+    int64_t ring_at, hist_at; // where ring and spike bits wait between launches
+    float unit, inv_unit;     // slots hold integers in this power of two (0: floats)
+    int32_t noise_at, pad;    // first value in a row of the noise drawn ahead (64 per group)
+};
+// Threads per workgroup and vertices per thread at most: with LIF vertices 128
+// registers per thread hold eight, with FP64 models 256 registers hold four.
+constexpr int kPushThreads = 1024, kPushMaxVpt = 8;
+constexpr int kPushThreadsFp64 = 512, kPushMaxVptFp64 = 4;
+
 // Host-side result of graph construction (before upload).
 struct HostGraph {
     int64_t n_total = 0, n_pad = 0;
@@ -270,7 +290,29 @@ struct EnsemblePlan {
     int32_t* wg_nets = nullptr;     // device: networks of workgroup b at [wg_off[b], wg_off[b+1])
     int32_t* wg_off = nullptr;      // device [blocks + 1]
     bool held = false;              // every workgroup holds one network of at most one chunk per wave
+    // push ensemble kernel (one workgroup per network)
+    bool push = false;
+    int vpt = 1;                    // vertices per thread of its instantiation (a power of two)
+    const PushNet* push_nets = nullptr;
+    const uint32_t* push_off = nullptr;
+    const uint32_t* push_edge = nullptr;
+    float* push_ring = nullptr;
+    uint64_t* push_hist = nullptr;
+    size_t push_ring_bytes = 0, push_hist_bytes = 0;
+    // noise drawn ahead (null: drawn in the steps): rows of noise_stride values for
+    // noise_steps steps, and the launch-order network of every 64 of them
+    double* noise = nullptr;
+    uint64_t* noise_pulses = nullptr;
+    const int32_t* noise_nets = nullptr;
+    int64_t noise_stride = 0;
+    int32_t noise_steps = 0;
 };
+// Noise is drawn ahead for ensembles that leave at least half the CUs idle, of
+// at most this many vertices (drawing a step's noise then takes the whole chip
+// a fraction of a microsecond; more of them fill the chip by themselves), and
+// for calls of at least this many steps (the launch it costs).
+constexpr int64_t kNoiseMaxVertices = 32768, kNoiseBytes = int64_t(64) << 20;
+constexpr int32_t kNoiseMinSteps = 16;
 
 // LDS bytes one network needs in the ensemble kernel.
 inline size_t ensemble_lds_bytes(int64_t n_nodes, int words, bool observe) {
@@ -312,6 +354,12 @@ hipError_t enable_ensemble_lds(size_t bytes);
 hipError_t launch_ensemble(const DeviceGraph& g, const EnsemblePlan& plan, int64_t t0, int32_t n_steps,
                            const net_record* rec, int32_t frame_num, int32_t frame_den, hipStream_t s,
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// Push ensemble kernel (ensemble_push.hip); models: 0 LIF only, 1 with
+// Izhikevich networks, 2 with Hodgkin-Huxley networks.
+hipError_t enable_push_ensemble(int models, int vpt, size_t lds_bytes);
+hipError_t launch_push_ensemble(const DeviceGraph& g, const EnsemblePlan& plan, int64_t t0, int32_t n_steps,
+                                const net_record* rec, int32_t frame_num, int32_t frame_den, hipStream_t s,
+                                hipEvent_t ev0, hipEvent_t ev1);
 
 // ---------------------------------------------------------------------------
 // Edge-scoring MLP 64 -> 256 -> 256 -> 1: flat FP32 parameter layout.
