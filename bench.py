@@ -577,15 +577,17 @@ def bench_graph(args, torch, synth, gn):
     """Launch-bound single networks (N = 256, config 0; N = 8,192 and
     65,536, config-1 density) stepped without records: plain per-step
     launches, the same kernels replayed from a captured 256-step HIP graph
-    (NET_BUILD_GRAPH), and the single-launch kernel (NET_BUILD_SINGLE_LAUNCH,
-    one launch per call), for the two-kernel and the fused step.  value =
+    (NET_BUILD_GRAPH), for the two-kernel and the fused step, the kernel that
+    keeps the network resident on the chip (no flags), and the single-launch
+    kernel (NET_BUILD_SINGLE_LAUNCH), one launch per call each.  value =
     steps/s of the N = 256 network with graph replays."""
     steps = args.graph_steps
     rows = []
-    cases = [("config0 N=256", synth.config0(), [0, gn.NET_BUILD_GRAPH, gn.NET_BUILD_SINGLE_LAUNCH])]
+    cases = [("config0 N=256", synth.config0(), [gn.NET_BUILD_PER_STEP, gn.NET_BUILD_GRAPH, 0, gn.NET_BUILD_SINGLE_LAUNCH])]
     for n in (8192, 65536):
         cases.append(("config1-density N=%d" % n, synth.config1(n=n),
-                      [0, gn.NET_BUILD_GRAPH, gn.NET_BUILD_FUSED_STEP, gn.NET_BUILD_FUSED_STEP | gn.NET_BUILD_GRAPH]))
+                      [gn.NET_BUILD_PER_STEP, gn.NET_BUILD_GRAPH, gn.NET_BUILD_FUSED_STEP | gn.NET_BUILD_PER_STEP,
+                       gn.NET_BUILD_FUSED_STEP | gn.NET_BUILD_GRAPH, 0]))
     for name, spec, variants in cases:
         for flags in variants:
             net = gn.Net(spec, flags=flags)

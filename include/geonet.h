@@ -168,7 +168,15 @@ typedef struct {
                                              delivers a spike) */
 #define NET_BUILD_DELIVER_NONTEMPORAL 4   /* delivery: non-temporal edge loads */
 #define NET_BUILD_PER_STEP 8              /* ensembles: per-step kernels instead of the
-                                             single-launch ensemble kernel */
+                                             single-launch ensemble kernel; one network: the per-step
+                                             kernels for every call.  (Otherwise one LIF network of up to
+                                             1,024 vertices per CU, built with none of the delivery flags
+                                             below but FUSED_STEP, PUSH, REORDER or AUTOTUNE and with every
+                                             sum exact, runs calls of 8 steps or more, outside a timing
+                                             window and not on a capturing stream, in one launch that keeps
+                                             it resident on the chip.  Same results; 8 B per edge and 4 B
+                                             per vertex and 256 (from 32,768 vertices on 512) vertices of
+                                             device memory more.) */
 #define NET_BUILD_DELIVER_UNROLL2 16      /* delivery: two 512-edge chunks per wave iteration
                                              (default one) */
 #define NET_BUILD_DELIVER_PIPELINE 128   /* delivery: issue the next chunk's edge loads while

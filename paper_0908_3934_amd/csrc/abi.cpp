@@ -35,6 +35,7 @@ struct net {
     int64_t t_every = 1;          // time one launch of each kind in t_every
     int64_t t_seen[4] = {0, 0, 0, 0};
     EnsemblePlan plan;
+    ResidentPlan resident;
     std::vector<int32_t> push_base;   // per network: first entry of its out-edge offsets, -1 if none
     std::vector<int32_t> drv_off;     // [n_nets + 1] each network's range of the ensemble's drive list
     bool autotuned = false;
@@ -49,6 +50,7 @@ struct net {
 };
 
 namespace {
+constexpr int64_t kResidentMinSteps = 8, kResidentMinRebuild = 128;
 constexpr int32_t kGraphSteps = 256;   // one replay: a whole turn of the history ring, an even number of steps
 }
 
@@ -135,6 +137,8 @@ void release_all(net* h) {
             (void)hipFree(p);
     }
     h->blocks.clear();
+    if (h->resident.fail) (void)hipHostFree(h->resident.fail);
+    h->resident.fail = nullptr;
 }
 
 template <typename T>
@@ -274,6 +278,26 @@ bool shape_push(net* h, int models, int threads, int groups_max, size_t lds_byte
     return true;
 }
 
+// The unit 2^*lg of integer input sums of network m: the smallest FP16 spacing
+// among its weights (of a value with exponent bits e: 2^(max(e, 1) - 25)).
+// Returns whether every row's sum of magnitudes fits 31 bits of it.
+bool weight_unit(const HostGraph& hg, int m, int* lg_out) {
+    const int64_t c0 = hg.net_chunk_begin[m], c1 = hg.net_chunk_end[m];
+    int lg = 16;
+    for (int64_t k = c0 * kChunkEdges; k < c1 * kChunkEdges; ++k)
+        if ((hg.w[k] & 0x7FFFu) != 0) lg = std::min(lg, std::max((hg.w[k] >> 10) & 31, 1) - 25);
+    int64_t sum = 0, most = 0;
+    for (int64_t k = c0 * kChunkEdges; k < c1 * kChunkEdges; ++k) {
+        if ((hg.rowstart[k >> 3] >> (k & 7)) & 1u) sum = 0;
+        const int e = (hg.w[k] >> 10) & 31;
+        const int64_t mant = (hg.w[k] & 0x3FF) | (e ? 0x400 : 0);
+        if (mant != 0) sum += mant << (std::max(e, 1) - 25 - lg);
+        most = std::max(most, sum);
+    }
+    *lg_out = lg;
+    return most < (int64_t(1) << 31);
+}
+
 // Tables and LDS layout of the push ensemble kernel; false (and nothing
 // uploaded) where a network fits neither its registers nor its LDS.  *st is
 // set when an upload failed.
@@ -355,25 +379,10 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
         }
     }
     for (int m = 0; m < n_nets; ++m) {
-        // The unit of the slots' integers: the smallest FP16 spacing among the
-        // network's weights, where every row's sum of magnitudes fits 31 bits
-        // of it (spacing of a value with exponent bits e: 2^(max(e, 1) - 25)).
-        PushNet& pn = nets[m];
-        int lg = 16;
-        for (int64_t k = hg.net_chunk_begin[m] * kChunkEdges; k < hg.net_chunk_end[m] * kChunkEdges; ++k)
-            if ((hg.w[k] & 0x7FFFu) != 0) lg = std::min(lg, std::max((hg.w[k] >> 10) & 31, 1) - 25);
-        int64_t sum = 0, most = 0;
-        for (int64_t c = hg.net_chunk_begin[m]; c < hg.net_chunk_end[m]; ++c)
-            for (int64_t k = c * kChunkEdges; k < (c + 1) * kChunkEdges; ++k) {
-                if ((hg.rowstart[k >> 3] >> (k & 7)) & 1u) sum = 0;
-                const int e = (hg.w[k] >> 10) & 31;
-                const int64_t mant = (hg.w[k] & 0x3FF) | (e ? 0x400 : 0);
-                if (mant != 0) sum += mant << (std::max(e, 1) - 25 - lg);
-                most = std::max(most, sum);
-            }
-        const bool fits = most < (int64_t(1) << 31);
-        pn.unit = fits ? std::ldexp(1.0f, lg) : 0.0f;
-        pn.inv_unit = fits ? std::ldexp(1.0f, -lg) : 0.0f;
+        int lg;
+        const bool fits = weight_unit(hg, m, &lg);
+        nets[m].unit = fits ? std::ldexp(1.0f, lg) : 0.0f;
+        nets[m].inv_unit = fits ? std::ldexp(1.0f, -lg) : 0.0f;
     }
     if (edge.empty()) edge.push_back(0u);
     // the costliest networks first: the workgroups that start last are short
@@ -421,6 +430,85 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
     pl.blocks = n_nets;
     pl.lds_bytes = *lds_need;
     return true;
+}
+
+// Shape and tables of the resident kernel for the handle's one network; left
+// disabled where it does not fit.
+//
+// Vertices per workgroup: 256, or 512 once those would be more than 128
+// workgroups (65,536 vertices, 128 steps: 256 each 522 us, 512 each 503 us,
+// 1,024 each 648 us; 8,192 vertices, 256 steps: 704, 748 and 1,080 us), beyond
+// 512 per CU as many as it takes, up to 1,024, the threads of a workgroup.
+net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
+    DeviceGraph& g = h->g;
+    ResidentPlan r;
+    int dev = 0, n_cu = 0, lds_max = 0, coop = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop || n_cu < 1)
+        return NET_OK;
+    const int64_t n = g.n_total;
+    r.n_local = static_cast<int>((std::max(std::min<int64_t>(std::max<int64_t>((n + 127) / 128, 256), 512), (n + n_cu - 1) / n_cu) + 63) / 64 * 64);
+    if (r.n_local > 1024 || hg.n_edges > (int64_t(1) << 28) || !(hg.row_abs_max < std::ldexp(1.0, 31 + hg.ulp_min)))
+        return NET_OK;
+    // sets of workgroups, one per XCD (the last groups may be left without vertices)
+    constexpr int kXcds = 8;
+    const int groups = static_cast<int>((n + r.n_local - 1) / r.n_local);
+    const int sets = groups > kXcds && (groups + kXcds - 1) / kXcds * kXcds <= n_cu ? kXcds : 1;
+    r.set_groups = (groups + sets - 1) / sets;
+    r.groups = r.set_groups * sets;
+    r.threads = std::max(r.n_local, 512);
+    const int64_t slots = (static_cast<int64_t>(lds_max) - 1024 - r.threads * 24) / (4 * r.n_local);   // (beside the waves' lists)
+    r.window = static_cast<int>(std::min<int64_t>(hg.max_delay, slots - 1));
+    if (r.window < 1 || !resident_fits(r, n_cu, static_cast<size_t>(lds_max))) return NET_OK;
+    r.unit = std::ldexp(1.0f, hg.ulp_min);
+    r.inv_unit = std::ldexp(1.0f, -hg.ulp_min);
+    // out-edges by (set, source, group of the target), made on the device, where
+    // at least as much memory is free beside them
+    const size_t n_off = static_cast<size_t>(sets) * static_cast<size_t>(n * r.set_groups) + 2;
+    uint32_t ring_slots = 1;
+    while (ring_slots <= static_cast<uint32_t>(hg.max_delay)) ring_slots <<= 1;
+    const size_t ring_words = h->lc.push ? 0 : static_cast<size_t>(ring_slots) * static_cast<size_t>(g.n_pad);
+    size_t mem_free = 0, mem_total = 0;
+    if (hipMemGetInfo(&mem_free, &mem_total) != hipSuccess ||
+        2 * (4 * n_off + 8 * static_cast<size_t>(hg.n_edges) + 4 * ring_words) > mem_free)
+        return NET_OK;
+    uint32_t *doff = nullptr, *sums = nullptr;
+    uint2* dedge = nullptr;
+    net_status st = zeros(h, &doff, n_off, s, "resident edges");
+    if (st == NET_OK) st = zeros(h, &dedge, static_cast<size_t>(std::max<int64_t>(hg.n_edges, 1)), s, "resident edges");
+    if (st == NET_OK) st = zeros(h, &sums, n_off / 4096 + 1, s, "resident edges");
+    if (st == NET_OK) st = zeros(h, &r.head, resident_head_words(r), s, "spike exchange");
+    if (st == NET_OK) st = zeros(h, &r.more, static_cast<size_t>(r.groups) * 2 * (1 + r.n_local / 32), s, "spike exchange");
+    if (st == NET_OK && !h->lc.push) {
+        r.ring_mask = ring_slots - 1;
+        st = zeros(h, &r.ring, ring_words, s, "arrival ring");
+    }
+    if (st == NET_OK) {
+        hipError_t e = launch_resident_tables(g, r, doff, static_cast<int64_t>(n_off), dedge, sums, hg.ulp_min, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) st = device_fail(h, e, "net_build: resident edges");
+    }
+    if (st != NET_OK) return st;
+    if (hipHostMalloc(reinterpret_cast<void**>(&r.fail), sizeof(uint32_t), hipHostMallocMapped) != hipSuccess ||
+        hipHostGetDevicePointer(reinterpret_cast<void**>(&r.fail_dev), r.fail, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        if (r.fail) (void)hipHostFree(r.fail);
+        return NET_OK;
+    }
+    *r.fail = 0u;
+    r.off = doff;
+    r.edge = dedge;
+    r.push = h->lc.push;
+    if (r.push) {
+        r.ring = g.in_ring;
+        r.ring_mask = g.in_ring_mask;
+    }
+    r.valid = true;                                     // (no arrivals yet)
+    r.enabled = true;
+    h->resident = r;
+    return NET_OK;
 }
 
 // Graph replays: the executable graph of a captured launch sequence.
@@ -540,6 +628,7 @@ net_status records_to_caller(net* h, const net_record* rec, int64_t rows, hipStr
 // The per-step kernels for n_steps steps (records optional), then the
 // step counter and the records' numbering.
 net_status step_loop(net* h, int64_t n_steps, const net_record* rec, hipStream_t s, bool observe) {
+    if (n_steps > 0) h->resident.valid = h->resident.push;   // (pull delivery leaves the arrivals' ring behind)
     for (int64_t k = 0; k < n_steps; ++k) {
         const int64_t t = h->t + k;
         hipEvent_t d0 = nullptr, d1 = nullptr, u0, u1;
@@ -575,6 +664,65 @@ net_status step_loop(net* h, int64_t n_steps, const net_record* rec, hipStream_t
         hipError_t e = launch_node_update(h->g, t, k, rec, flush, frame, steps, s, u0, u1);
         if (e != hipSuccess) return device_fail(h, e, "net_step_n: update launch");
     }
+    h->t += n_steps;
+    return records_to_caller(h, rec, n_steps, s);
+}
+
+// Whether a call of n_steps goes to the resident kernel.  Its launch costs
+// about 20 us more than a step's kernels (8 us to 13 us a step against 2 to 4):
+// calls below kResidentMinSteps stay with those, and where the ring of
+// arrivals has to be rebuilt first (about 100 us), calls below
+// kResidentMinRebuild.  A timing window times the step's kernels; a stream that
+// is being captured records them, and since its replays move the state unseen,
+// the handle then keeps to them.
+bool resident_route(net* h, int64_t n_steps, hipStream_t s) {
+    ResidentPlan& r = h->resident;
+    if (!r.enabled || n_steps < (r.valid ? kResidentMinSteps : kResidentMinRebuild) || h->t_cap != 0) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        r.enabled = false;
+        return false;
+    }
+    return true;
+}
+
+// A resident call ended at a wait's limit: the state it left is no step's.
+bool lost_workgroups(net* h) {
+    if (!h->resident.fail || __atomic_load_n(h->resident.fail, __ATOMIC_RELAXED) == 0u) return false;
+    h->broken = true;
+    return true;
+}
+
+net_status step_resident(net* h, int64_t n_steps, const net_record* rec, hipStream_t s) {
+    ResidentPlan& r = h->resident;
+    if (!r.valid) {
+        const hipError_t e = launch_resident_rebuild(h->g, r, h->t, s);
+        if (e != hipSuccess) return device_fail(h, e, "net_step_n: arrivals");
+        r.valid = true;
+    }
+    for (int64_t done = 0; done < n_steps;) {
+        const int32_t chunk = static_cast<int32_t>(std::min<int64_t>(n_steps - done, int64_t(1) << 29));
+        net_record sub{};
+        if (rec) {
+            const int64_t words = (h->g.n_total + 63) / 64;
+            sub.raster = rec->raster ? rec->raster + done * words : nullptr;
+            sub.v = rec->v ? rec->v + done * h->g.n_total : nullptr;
+            sub.input = rec->input ? rec->input + done * h->g.n_total : nullptr;
+        }
+        // the step sequence starts again before its 31-bit tags could meet
+        // themselves (the first words' 16-bit tags, written every step, go on)
+        hipError_t e = hipSuccess;
+        if (r.seq >= (1u << 30)) {
+            e = launch_resident_renumber(r, s);
+            r.seq = (r.seq & 0xFFFFu) + 0x10000u;
+        }
+        if (e == hipSuccess) e = launch_resident(h->g, r, h->t + done, chunk, rec ? &sub : nullptr, h->frame_num, h->frame_den, s);
+        if (e != hipSuccess) return device_fail(h, e, "net_step_n: resident launch");
+        r.seq += static_cast<uint32_t>(chunk);
+        done += chunk;
+    }
+    advance_frames(h, h->t, n_steps);
     h->t += n_steps;
     return records_to_caller(h, rec, n_steps, s);
 }
@@ -1267,6 +1415,14 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
         }
         h->autotuned = best >= 0;
     }
+    // the resident kernel, unless the caller chose among the per-step kernels
+    constexpr int kChosen = NET_BUILD_NO_LDS_SUMMARY | NET_BUILD_DELIVER_STREAM_WEIGHTS | NET_BUILD_DELIVER_NONTEMPORAL |
+                            NET_BUILD_PER_STEP | NET_BUILD_DELIVER_UNROLL2 | NET_BUILD_DELIVER_PIPELINE | NET_BUILD_SUMMARY_HALF |
+                            NET_BUILD_DELIVER_COMPACT | NET_BUILD_DELIVER_PACKED | NET_BUILD_GRAPH;
+    if (n_nets == 1 && !h->plan.enabled && !hg.plastic && !hg.any_izh && !hg.any_hh && hg.exact && !(bflags & kChosen) &&
+        !(opts && (opts->block_threads || opts->blocks_per_cu)) && (frame_cap == 0 || hg.frame_num > 0) &&
+        (st = plan_resident(h, hg, s)) != NET_OK)
+        return bail(st);
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         device_fail(h, e, "net_build: upload");
@@ -1287,6 +1443,8 @@ net_status net_step_n(net_t* h, int64_t n_steps, const net_record* rec, void* st
     hipStream_t s = static_cast<hipStream_t>(stream);
     h->last_stream = s;
     const bool observe = h->g.frame_cap > 0 && h->frame_num > 0;
+    if (lost_workgroups(h)) return fail(NET_E_DEVICE, "net_step_n: the workgroups of an earlier call lost each other");
+    if (resident_route(h, n_steps, s)) return step_resident(h, n_steps, rec, s);
     // graph replays: no records, no kernel timing
     const bool graphs = h->graph && !rec && h->t_cap == 0 && n_steps > 0;
     if (graphs && h->plan.enabled) {
@@ -1361,6 +1519,7 @@ net_status net_step_n(net_t* h, int64_t n_steps, const net_record* rec, void* st
 
 net_status net_observe(net_t* h, int32_t what, const void* params, void* out, int64_t out_bytes, void* stream) {
     if (!h) return fail(NET_E_ARG, "net_observe: handle is NULL");
+    if (lost_workgroups(h)) return fail(NET_E_DEVICE, "net_observe: the workgroups of an earlier call lost each other");
     if (h->broken) return fail(NET_E_STATE, "net_observe: handle unusable after a device error");
     if (!out) return fail(NET_E_ARG, "net_observe: out is NULL");
     const int64_t n = h->g.n_total;

@@ -447,6 +447,8 @@ net_status build_host_graph(const net_desc* descs, int32_t n_nets, HostGraph& g,
             ulp_min = std::min(ulp_min, fp16_ulp_log2(g.w[s]));
         }
         if (sum_abs > 0.0 && sum_abs > std::ldexp(two24, ulp_min)) g.exact = false;
+        g.ulp_min = std::min(g.ulp_min, ulp_min);
+        g.row_abs_max = std::max(g.row_abs_max, sum_abs);
     }
     if (track) {
         // plastic weights: integer multiples of 2^-20 (exact sums in any order)

@@ -69,52 +69,7 @@ struct PushArgs {
     int32_t n_steps, frame_cap, frame_num, frame_den;
 };
 
-// Barrier that orders LDS only (records on their way to memory are not waited for).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-__device__ __forceinline__ uint64_t read_lane64(uint64_t v, int lane) {
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(v), lane);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(v >> 32), lane);
-    return lo | (static_cast<uint64_t>(hi) << 32);
-}
-
-// The offset table is never written while the kernel runs: uniform entries of
-// it are scalar loads.
-typedef const uint32_t __attribute__((address_space(4)))* const_words;
-
-// The kernel's arguments, read again where they are used: a pointer the
-// compiler cannot see through keeps the dozens that only the start, the end or
-// a rare branch needs out of scalar registers while the steps run.
 typedef const PushArgs __attribute__((address_space(4)))* const_args;
-template <class P>
-__device__ __forceinline__ P reread(P p) {
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
-// A wave-uniform value that the compiler takes for a new one each time.
-__device__ __forceinline__ uint32_t opaque(uint32_t x) {
-    x = __builtin_amdgcn_readfirstlane(x);
-    asm volatile("" : "+s"(x));
-    return x;
-}
-
-// A struct in memory that no kernel writes, by scalar loads (`p` is uniform).
-template <class T>
-__device__ __forceinline__ T load_const(const T* p) {
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    const const_words w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(p));
-    uint32_t words[sizeof(T) / 4];
-#pragma unroll
-    for (size_t i = 0; i < sizeof(T) / 4; ++i) words[i] = w[i];
-    T v;
-    __builtin_memcpy(&v, words, sizeof(T));
-    return v;
-}
 
 // What a wave keeps of its network while the steps run (all wave-uniform but
 // `lane`).
@@ -194,20 +149,6 @@ __device__ __forceinline__ bool push_spikes(const State& S, int q, const NetPara
     if constexpr (kModel == NET_MODEL_LIF) return S.V[q] >= p.v_th;
     else if constexpr (kModel == NET_MODEL_IZHIKEVICH) return S.st[q].v >= static_cast<double>(p.v_th);
     else return S.st[q].v >= static_cast<double>(p.v_th) && S.st[q].vprev < static_cast<double>(p.v_th);
-}
-
-// Sum of x over the lanes below this one; *total over all (DPP row shifts and
-// row broadcasts).
-__device__ __forceinline__ uint32_t wave_prefix(uint32_t x, uint32_t* total) {
-    uint32_t s = x;
-    s += __builtin_amdgcn_update_dpp(0u, s, 0x111, 0xF, 0xF, false);   // row_shr:1
-    s += __builtin_amdgcn_update_dpp(0u, s, 0x112, 0xF, 0xF, false);   // row_shr:2
-    s += __builtin_amdgcn_update_dpp(0u, s, 0x114, 0xF, 0xF, false);   // row_shr:4
-    s += __builtin_amdgcn_update_dpp(0u, s, 0x118, 0xF, 0xF, false);   // row_shr:8
-    s += __builtin_amdgcn_update_dpp(0u, s, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
-    s += __builtin_amdgcn_update_dpp(0u, s, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
-    *total = __builtin_amdgcn_readlane(s, 63);
-    return s - x;
 }
 
 // How a network's noise comes: it has none, or every wave draws its own, or

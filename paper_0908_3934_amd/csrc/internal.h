@@ -121,6 +121,8 @@ struct HostGraph {
     int32_t max_delay = 1;
     int32_t window = 1;           // recent-spike summary window (steps)
     bool exact = true;
+    int32_t ulp_min = 16;         // smallest spacing 2^ulp_min among the FP16 weights that are not zero
+    double row_abs_max = 0.0;     // largest row sum of weight magnitudes
     std::vector<int32_t> src;     // [e_slots]
     std::vector<uint16_t> w;      // [e_slots] FP16 bits
     std::vector<uint8_t> d;       // [e_slots]
@@ -313,6 +315,37 @@ struct EnsemblePlan {
 // for calls of at least this many steps (the launch it costs).
 constexpr int64_t kNoiseMaxVertices = 32768, kNoiseBytes = int64_t(64) << 20;
 constexpr int32_t kNoiseMinSteps = 16;
+
+// One network resident on the chip for the steps of a call (resident.hip).
+constexpr uint32_t kResidentFar = 0x80000000u;
+struct ResidentPlan {
+    bool enabled = false;
+    bool push = false;              // its ring is the push delivery's (else its own, see `valid`)
+    bool valid = false;             // the ring holds the arrivals to come (pull delivery keeps spikes instead)
+    int groups = 0, set_groups = 0, threads = 0;   // workgroups, those of a set, and their threads
+    int n_local = 0;                // vertices per workgroup
+    int window = 0;                 // steps of arrivals in LDS
+    uint32_t ring_mask = 0, seq = 2;
+    const uint32_t* off = nullptr;  // device [groups / set_groups][n_total][set_groups], and one more
+    const uint2* edge = nullptr;    // device: (delay n_local + target in its group, or beyond the window
+                                    // kResidentFar | delay << 16 | target; weight in units)
+    float* ring = nullptr;          // device [ring_mask + 1][n_pad]
+    uint64_t* head = nullptr;
+    uint64_t* more = nullptr;
+    uint32_t* fail = nullptr;       // host memory and its device address
+    uint32_t* fail_dev = nullptr;
+    float unit = 0.0f, inv_unit = 0.0f;
+};
+bool resident_fits(const ResidentPlan& r, int n_cu, size_t lds_max);
+size_t resident_head_words(const ResidentPlan& r);
+// Out-edge tables of the resident kernel from the handle's edges (off: zero; lg: the weights' unit is 2^lg).
+hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, uint32_t* off, int64_t n_off, uint2* edge, uint32_t* sums,
+                                  int lg, hipStream_t s);
+// Clears the words whose tags a restarted step sequence could meet again.
+hipError_t launch_resident_renumber(const ResidentPlan& r, hipStream_t s);
+hipError_t launch_resident_rebuild(const DeviceGraph& g, const ResidentPlan& r, int64_t t, hipStream_t s);
+hipError_t launch_resident(const DeviceGraph& g, const ResidentPlan& r, int64_t t0, int32_t n_steps, const net_record* rec,
+                           int32_t frame_num, int32_t frame_den, hipStream_t s);
 
 // LDS bytes one network needs in the ensemble kernel.
 inline size_t ensemble_lds_bytes(int64_t n_nodes, int words, bool observe) {

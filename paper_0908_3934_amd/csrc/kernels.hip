@@ -656,20 +656,7 @@ __device__ __forceinline__ void vertex_update(const NodeArgs& a, int64_t j, int6
     }
     // recent-spike summary for the next step: last spike within d_sum steps
     const uint64_t recent = wave_ballot(valid && age_n <= static_cast<uint32_t>(a.d_sum));
-    if (lane == 0 && j < word_end && !a.out_edge) {   // (push delivery needs no summary)
-        if (a.sum_shift == 0) {
-            reinterpret_cast<uint64_t*>(a.summary)[j >> 6] = recent;
-        } else {
-            // one bit per vertex pair: OR the pairs, then pack the even bits
-            uint64_t x = (recent | (recent >> 1)) & 0x5555555555555555ull;
-            x = (x | (x >> 1)) & 0x3333333333333333ull;
-            x = (x | (x >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-            x = (x | (x >> 4)) & 0x00FF00FF00FF00FFull;
-            x = (x | (x >> 8)) & 0x0000FFFF0000FFFFull;
-            x = (x | (x >> 16)) & 0x00000000FFFFFFFFull;
-            a.summary[j >> 6] = static_cast<uint32_t>(x);
-        }
-    }
+    if (lane == 0 && j < word_end && !a.out_edge) put_summary(a.summary, j, recent, a.sum_shift);   // (push delivery needs none)
 
     if (valid) {
         a.V[j] = vn;

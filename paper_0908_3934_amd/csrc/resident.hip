@@ -1,0 +1,749 @@
+// One large LIF network resident on the chip for all steps of a call: every
+// workgroup owns a range of vertices (state in registers, arriving input in
+// LDS) and the workgroups exchange each step's spikes through memory.
+//
+// Exchange.  A workgroup publishes its spikes of step t + 1 as soon as step t
+// has updated its vertices: a word with a tag of the step, their number and up to
+// four vertex indices; up to four more are in a second word, and where still more
+// fire, one tagged word per 32 vertices.
+// Every workgroup reads every other's word, again until its tag is the step's,
+// and the others as the number says.  A word is one 8-byte access, so it needs no order towards any other;
+// two sets in turn are enough, since a workgroup publishes t + 2 only after it
+// has read all words of t + 1, which their owners publish after reading all of
+// t.  The launch is cooperative (all workgroups are on the chip together), and
+// every wait has a limit, after which the launch ends and the handle fails.
+//
+// Delivery.  Out-edges are kept by (set of workgroups, source, workgroup of the
+// target), so a workgroup finds its part of a spike's edges with one load of
+// two offsets.  A set is the workgroups of one XCD (block b runs on XCD b mod
+// 8), next to each other in vertex order: they look up the same sources at the
+// same time, and a source's offsets for all of them are one line of their L2.
+// Arrivals up to W steps ahead are added into LDS as integers in units of the
+// weights' smallest FP16 spacing (exact, as the FP32 sums are; see
+// ensemble_push.hip for the LDS atomics' cost); later ones go into the ring of
+// arrival steps in memory that push delivery uses, whose slot of step t + W
+// the owner takes over at step t.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "internal.h"
+#include "philox.h"
+#include "vertex.h"
+
+namespace geonet {
+namespace {
+
+constexpr int kHeadIds = 4, kMoreIds = 3;         // vertex indices in the first and in the second word
+// First words stand 128 bytes apart: in a shared line one workgroup's store
+// waits for the others' and for every poll of them (an exchange alone among 256
+// workgroups: 1.12 us against 1.67 with 16 words a line; among 32, 0.99 against
+// 1.33).
+constexpr int kHeadStep = 16;
+constexpr uint32_t kMoreTag = 0x7FFFFFFFu;        // (a second word may stand for long: a long tag)
+constexpr int kListWords = 64 * kHeadIds + 128;   // a wave's list of spikes, of workgroups, and deliver_spikes' words
+constexpr uint32_t kHeadMany = 15u;               // its count where they do not fit
+constexpr uint32_t kFar = kResidentFar;
+constexpr uint32_t kSpinLimit = 1u << 22;         // polls (a few seconds)
+
+struct RunArgs {
+    const uint32_t* __restrict__ off;   // [sets][n_total][set_groups] and one more: first edge
+    const uint2* __restrict__ edge;     // (delay n_local + target in the group, or for delays beyond the window kFar |
+                                        // delay << 16 | target; weight in units)
+    float* ring;                        // [ring_mask + 1][n_pad] arrivals by step
+    uint64_t* head;                     // [2][groups] first words, kHeadStep apart
+    uint64_t* more;                     // [2][groups] second words, then [2][groups][n_local / 32] words of spike bits
+    uint32_t* fail;                     // host memory: set where a wait reached its limit
+    float* __restrict__ V;
+    uint16_t* __restrict__ age;
+    uint32_t* __restrict__ hist;        // pull delivery's spike history and summary (else null)
+    uint32_t* __restrict__ summary;
+    const uint32_t* __restrict__ drive_thr;
+    const float* __restrict__ i_ext;
+    double* __restrict__ calcium;
+    double* __restrict__ frame_acc;
+    float* __restrict__ frames;
+    uint64_t* __restrict__ rec_raster;
+    float* __restrict__ rec_v;
+    float* __restrict__ rec_input;
+    const int32_t* __restrict__ caller_of;
+    const NetParams* __restrict__ params;
+    int64_t t0, n_total, n_pad, raster_words;
+    uint32_t ring_mask, seq0;
+    int32_t n_steps, n_local, set_groups, window, max_delay, d_sum, sum_shift, frame_cap, frame_num, frame_den;
+    float unit, inv_unit;
+};
+
+typedef const RunArgs __attribute__((address_space(4)))* const_args;
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+}
+
+// Polls a published word until the low `bits` bits of it are the tag.
+__device__ __forceinline__ uint64_t poll_word(const uint64_t* at, bool want, uint32_t tag, uint32_t tag_mask, bool* dead) {
+    uint64_t v = tag;
+    bool wait = want;
+#pragma unroll 1
+    for (uint32_t spin = 0; wave_ballot(wait) != 0; ++spin) {
+        if (wait) {
+            v = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait = (static_cast<uint32_t>(v) & tag_mask) != tag;
+        }
+        if (*dead || spin >= kSpinLimit) {
+            *dead = true;
+            break;
+        }
+    }
+    return wait ? tag : v;       // (given up: no spikes)
+}
+
+struct RunCtx {
+    const uint32_t* off;     // this workgroup's offsets, `step` apart
+    uint32_t step;
+    const uint2* edge;
+    float* ring;             // this workgroup's first vertex in the ring's slot 0
+    int* slots;
+    int64_t n_pad;
+    uint32_t ring_mask, size;   // (W + 1) n_local
+    int lane;
+    float unit;
+};
+
+// `now`: slot of step t x n_local
+__device__ __forceinline__ void add_edge(const RunCtx& c, uint2 e, uint32_t now, uint32_t t) {
+    if (!(e.x & kFar)) {
+        const uint32_t at = now + e.x;
+        atomicAdd(c.slots + (at < at - c.size ? at : at - c.size), static_cast<int>(e.y));
+    } else {
+        // (only this workgroup's waves touch these entries while the kernel runs)
+        const uint32_t d = (e.x >> 16) & 0xFFu, to = e.x & 0xFFFFu;
+        __hip_atomic_fetch_add(c.ring + static_cast<int64_t>((t + d) & c.ring_mask) * c.n_pad + to,
+                               static_cast<float>(static_cast<int>(e.y)) * c.unit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+// Delivers this workgroup's part of up to 64 spikes, one per lane (`have`).
+// Most have no edge here or a few: the edges of all lists are numbered through,
+// and the wave takes 64 of them at a time, four such loads in flight (`flat`:
+// 64 words of the wave's own).  With a lane per list up to four edges long and
+// the wave per longer one, a step of 262,144 vertices with 11,750 spikes took
+// 87 us, now 78 (65,536 vertices with 2,890 spikes: 25.3 and 19.5).
+__device__ __forceinline__ void deliver_spikes(const RunCtx& c, bool have, uint32_t src, uint32_t now, uint32_t t, uint32_t* flat) {
+    constexpr int kLoads = 4;
+    uint32_t e0 = 0u, len = 0u;
+    if (have) {
+        uint32_t range[2];
+        __builtin_memcpy(range, c.off + static_cast<size_t>(src) * c.step, sizeof(range));
+        e0 = range[0];
+        len = range[1] - range[0];
+    }
+    const uint64_t lists = wave_ballot(len != 0u);
+    if (lists == 0) return;
+    uint32_t total;
+    const uint32_t at = wave_prefix(len, &total);                      // the number of the list's first edge
+    const bool one = (lists & (lists - 1)) == 0;
+    const uint32_t e_one = __builtin_amdgcn_readlane(e0, __builtin_ctzll(lists));
+    const uint32_t lane = static_cast<uint32_t>(c.lane);
+    for (uint32_t n0 = 0; n0 < total; n0 += 64u * kLoads) {
+        uint2 rec[kLoads];
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            const uint32_t n = n0 + 64u * q;
+            rec[q] = make_uint2(0u, 0u);
+            if (n >= total) continue;
+            uint32_t e = e_one + n + lane;
+            if (!one) {
+                // the first edge here of every list that reaches into these 64, at its place;
+                // the others follow the nearest one below them
+                flat[lane] = ~0u;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                const uint32_t lo = at > n ? at : n;
+                if (len != 0u && lo < n + 64u && at + len > n) flat[lo - n] = e0 + (lo - at);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                const uint32_t x = flat[lane];
+                const uint64_t heads = wave_ballot(x != ~0u);
+                const int head = 63 - __builtin_clzll(heads & (~0ull >> (63 - c.lane)));
+                e = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(head << 2, static_cast<int>(x))) + (lane - static_cast<uint32_t>(head));
+            }
+            if (n + lane < total) rec[q] = c.edge[e];
+        }
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            if (n0 + 64u * q >= total) break;
+            if (rec[q].y != 0u) add_edge(c, rec[q], now, t);
+        }
+    }
+}
+
+// What bounds it: the exchange (a word takes about 1 us from one workgroup to
+// all others at 8 workgroups, 2 us at 256) and the two dependent loads of the
+// spikes' edges; noise is drawn while the words are on their way.  us per step,
+// one launch or two per step before and now (noise 0.05, 3-D, about 100 in-edges
+// a vertex, 0.5 spikes a step and 1,000 vertices): 8,192 vertices 7.6 / 2.7;
+// 65,536 (pull delivery before) 13.0 / 3.9; 262,144 (push before) 6.5 / 4.8.
+// At the most spikes a network can have (one in 22 vertices a step) 8,192: 9.2 /
+// 6.8 (push before 7.4), 65,536: 30 / 19.5 (21), 262,144: 81 / 78.
+__global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
+    extern __shared__ uint4 lds4[];
+    __shared__ uint64_t s_words[2][16];
+    __shared__ uint32_t s_dead;
+    (void)args;
+    const const_args ka = (const_args)__builtin_amdgcn_kernarg_segment_ptr();
+    const_args a = reread(ka);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = static_cast<int>(blockDim.x >> 6);
+    const int groups = static_cast<int>(gridDim.x), sets = groups / a->set_groups;
+    const int set = static_cast<int>(blockIdx.x) % sets, in_set = static_cast<int>(blockIdx.x) / sets;
+    const int b = set * a->set_groups + in_set;                        // this workgroup's place in vertex order
+    const uint32_t W = static_cast<uint32_t>(a->window);
+    const int n_local = a->n_local;
+    const int own_words = n_local >> 6;                                 // words of 64 vertices; wave w has w, w + waves, ..
+    const int64_t n_total = a->n_total, j0 = static_cast<int64_t>(b) * n_local;
+    const NetParams p = load_const(a->params);
+    RunCtx c;
+    c.off = a->off + static_cast<int64_t>(set) * n_total * a->set_groups + in_set;
+    c.step = static_cast<uint32_t>(a->set_groups);
+    c.edge = a->edge;
+    c.ring = a->ring + j0;
+    c.slots = reinterpret_cast<int*>(lds4);
+    c.n_pad = a->n_pad;
+    c.ring_mask = a->ring_mask;
+    c.size = (W + 1u) * static_cast<uint32_t>(n_local);
+    c.lane = lane;
+    c.unit = a->unit;
+    const float inv_unit = a->inv_unit;
+    uint32_t* list = reinterpret_cast<uint32_t*>(c.slots + (W + 1u) * static_cast<uint32_t>(n_local)) + wave * kListWords;
+    uint32_t *who = list + 64 * kHeadIds, *flat = who + 64;
+    const uint32_t many_words = static_cast<uint32_t>(n_local) >> 5;
+    const int64_t t0_64 = a->t0;
+    const uint32_t t0 = static_cast<uint32_t>(t0_64), seq0 = a->seq0;
+    const int32_t n_steps = a->n_steps;
+
+    // ---- state in: the arrivals of steps t0 .. t0 + W - 1 move to LDS
+    if (tid == 0) s_dead = 0u;
+    const uint32_t slot0 = static_cast<uint32_t>(static_cast<uint64_t>(t0_64) % (W + 1u));
+    const uint32_t quads = static_cast<uint32_t>(n_local) >> 2;         // (four vertices at a time, four such loads in flight)
+    for (uint32_t i0 = tid; i0 < (W + 1u) * quads; i0 += 4u * blockDim.x) {
+        float4 x[4];
+        float4* at[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t i = i0 + q * blockDim.x, k = i / quads, v = (i - k * quads) * 4u;
+            x[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            at[q] = reinterpret_cast<float4*>(c.ring + static_cast<int64_t>((t0 + k) & c.ring_mask) * c.n_pad + v);
+            if (k < W && j0 + v < c.n_pad) x[q] = *at[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t i = i0 + q * blockDim.x, k = i / quads, v = (i - k * quads) * 4u;
+            if (k > W) continue;
+            if (x[q].x != 0.0f || x[q].y != 0.0f || x[q].z != 0.0f || x[q].w != 0.0f) *at[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const uint32_t s = slot0 + k > W ? slot0 + k - (W + 1u) : slot0 + k;
+            *reinterpret_cast<int4*>(c.slots + s * static_cast<uint32_t>(n_local) + v) =
+                make_int4(static_cast<int>(x[q].x * inv_unit), static_cast<int>(x[q].y * inv_unit),
+                          static_cast<int>(x[q].z * inv_unit), static_cast<int>(x[q].w * inv_unit));
+        }
+    }
+    // (255 or more steps back: as good as never)
+    const bool obs = a->calcium != nullptr, pulls = a->hist != nullptr;
+    const int64_t j = j0 + tid;                                         // this thread's vertex
+    const bool owns = wave < own_words, valid = owns && j < n_total;
+    float V = 0.0f, iext = 0.0f;
+    uint32_t last = t0 - 255u, prev = t0 - 255u, thr = 0u, jl = 0u, bits = 0u;
+    double cal = 0.0, acc = 0.0;
+    if (valid) {
+        V = a->V[j];
+        const uint32_t ages = a->age[j];
+        last = t0 - (ages & 0xFFu);
+        prev = t0 - (ages >> 8);
+        thr = a->drive_thr ? a->drive_thr[j] : 0u;
+        iext = a->i_ext ? a->i_ext[j] : 0.0f;
+        jl = static_cast<uint32_t>(a->caller_of ? a->caller_of[j] : j);
+        if (pulls) bits = a->hist[static_cast<int64_t>((t0 & 0xFFu) >> 5) * c.n_pad + j];
+        if (obs) {
+            cal = a->calcium[j];
+            acc = a->frame_acc[j];
+        }
+    }
+    uint64_t spk = wave_ballot(valid && V >= p.v_th);                   // this wave's spikes of the step to come
+    const bool draws = owns && (wave_ballot(thr != 0u) != 0 || p.sigma != 0.0f);
+    const bool far = static_cast<uint32_t>(a->max_delay) > W;
+    uint64_t* raster = a->rec_raster && owns && lane == 0 && j < n_total ? a->rec_raster + (j >> 6) : nullptr;
+    const int64_t raster_words = a->raster_words;
+    const uint32_t records = a->rec_v || a->rec_input ? 1u : 0u;       // (opaque in the loop: not copied for both cases)
+    uint64_t* const head = a->head;
+    // the workgroup whose word this lane reads: every wave has as many, from all
+    // over the network and from no regular places of it, since this one's
+    // neighbours, in vertex order a power of two away, have the long lists
+    const int asks = lane * waves + (wave + 5 * lane) % waves;
+    const bool want = lane < (groups + waves - 1) / waves && asks < groups;
+    const int my_group = want ? asks : 0;
+    uint32_t slot = slot0;
+    int64_t frame = 0, next_flush = INT64_MAX, frame_first = 0;
+    if (obs) {
+        frame = t0_64 * a->frame_num / a->frame_den;
+        frame_first = (frame * a->frame_den + a->frame_num - 1) / a->frame_num;
+        next_flush = ((frame + 1) * a->frame_den + a->frame_num - 1) / a->frame_num;
+    }
+
+    // this workgroup's spikes of the step whose sequence number is `seq`
+    auto publish = [&](uint32_t seq) {
+        const uint32_t par = seq & 1u;
+        if (lane == 0 && owns) s_words[par][wave] = spk;
+        lds_barrier();
+        if (wave != 0) return;
+        const uint64_t word = lane < own_words ? s_words[par][lane] : 0;
+        uint64_t some = wave_ballot(word != 0);
+        uint64_t h0 = 0, h1 = 0;                                        // count from bit 16, indices from bits 20 and 31
+        uint32_t n = 0;
+        for (; some != 0 && n <= kHeadIds + kMoreIds; some &= some - 1) {
+            const int w = __builtin_ctzll(some);
+            for (uint64_t m = read_lane64(word, w); m != 0 && n <= kHeadIds + kMoreIds; m &= m - 1, ++n) {
+                const uint64_t id = static_cast<uint64_t>(w * 64 + __builtin_ctzll(m));
+                if (n < kHeadIds) h0 |= id << (20 + 11 * n);
+                else if (n < kHeadIds + kMoreIds) h1 |= id << (31 + 11 * (n - kHeadIds));
+            }
+        }
+        h0 |= static_cast<uint64_t>(n > kHeadIds + kMoreIds ? kHeadMany : n) << 16;
+        if (n > kHeadIds) {
+            // more than the first word holds: the second, or all words
+            uint64_t* const more = reread(ka)->more;
+            if (n <= kHeadIds + kMoreIds) {
+                if (lane == 0)
+                    __hip_atomic_store(more + static_cast<int64_t>(par) * groups + b, h1 | (seq & kMoreTag), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            } else if (lane < own_words) {
+                uint64_t* to = more + 2 * groups + (static_cast<int64_t>(par) * groups + b) * (n_local >> 5) + 2 * lane;
+                __hip_atomic_store(to, word << 32 | (seq & kMoreTag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(to + 1, (word >> 32) << 32 | (seq & kMoreTag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (lane == 0)
+            __hip_atomic_store(head + (static_cast<int>(par) * groups + b) * kHeadStep, h0 | (seq & 0xFFFFu), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                    // the ring's entries taken over are cleared
+    publish(seq0);
+
+    int32_t row = 0;
+    for (int32_t k = 0; k < n_steps; ++k) {
+        const uint32_t seq = seq0 + static_cast<uint32_t>(k), par = seq & 1u;
+        const uint32_t t = t0 + static_cast<uint32_t>(k);
+        // the ring's arrivals of step t + W (no push reaches that step's entries any
+        // more) and the noise, drawn before the first look at the words: looking
+        // before they are there only delays them
+        float late = 0.0f, noise = 0.0f;
+        bool pulse = false;
+        if (far && valid)
+            late = __hip_atomic_exchange(c.ring + static_cast<int64_t>((t + W) & c.ring_mask) * c.n_pad + tid, 0.0f,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (draws) {
+            const uint4 r = philox4x32_10(make_uint4(jl, t, static_cast<uint32_t>(static_cast<uint64_t>(t0_64 + k) >> 32), 0u),
+                                          opaque(p.key_lo), opaque(p.key_hi));
+            pulse = r.x < thr;
+            if (p.sigma != 0.0f) noise = p.sigma * gaussian(r.y, r.z);
+        }
+        // ---- every workgroup's spikes of the step
+        bool dead = false;
+        {
+            const uint64_t v = poll_word(head + (static_cast<int>(par) * groups + my_group) * kHeadStep, want, seq & 0xFFFFu,
+                                         0xFFFFu, &dead);
+            const uint32_t n = want ? static_cast<uint32_t>(v >> 16) & 15u : 0u;
+            const uint32_t base = static_cast<uint32_t>(my_group * n_local);
+            uint32_t total = 0, r0 = 0;                     // the wave's spikes in its list, those delivered
+            uint32_t asked = 0, to_ask = 0;                 // words of 32 vertices of the workgroups with too many for theirs
+            uint32_t left = 0, left0 = 0;                   // such a word's spikes still to be listed, its first vertex
+            bool direct = wave_ballot(n != 0u) != 0;        // a spike per lane at most: straight from the words
+            if (wave_ballot(n > 1u) != 0) {
+                direct = false;
+                const uint32_t in_first = n == kHeadMany ? 0u : (n < kHeadIds ? n : kHeadIds);
+#pragma unroll
+                for (int q = 0; q < kHeadIds; ++q) {
+                    const bool has = static_cast<uint32_t>(q) < in_first;
+                    const uint64_t m = wave_ballot(has);
+                    if (has) list[total + lanes_below(m)] = base + (static_cast<uint32_t>(v >> (20 + 11 * q)) & 0x7FFu);
+                    total += static_cast<uint32_t>(__popcll(m));
+                }
+                const bool second = n > kHeadIds && n != kHeadMany;
+                if (wave_ballot(second) != 0) {
+                    const uint64_t v1 = poll_word(reread(ka)->more + static_cast<int64_t>(par) * groups + my_group, second,
+                                                  seq & kMoreTag, kMoreTag, &dead);
+#pragma unroll
+                    for (int q = 0; q < kMoreIds; ++q) {
+                        const bool has = second && !dead && q + kHeadIds < n;
+                        const uint64_t m = wave_ballot(has);
+                        if (has) list[total + lanes_below(m)] = base + (static_cast<uint32_t>(v1 >> (31 + 11 * q)) & 0x7FFu);
+                        total += static_cast<uint32_t>(__popcll(m));
+                    }
+                }
+                const uint64_t many = wave_ballot(n == kHeadMany);
+                if (n == kHeadMany) who[lanes_below(many)] = static_cast<uint32_t>(my_group);
+                to_ask = static_cast<uint32_t>(__popcll(many)) * many_words;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+            }
+            // up to 64 spikes at a time, one per lane
+            while (true) {
+                bool have;
+                uint32_t src = 0u;
+                if (direct) {
+                    have = n != 0u;
+                    src = base + (static_cast<uint32_t>(v >> 20) & 0x7FFu);
+                    direct = false;
+                } else if (r0 < total) {
+                    have = r0 + lane < total;
+                    if (have) src = list[r0 + lane];
+                    r0 += 64u;
+                } else if (wave_ballot(left != 0u) != 0) {
+                    // up to four spikes of every lane's word
+                    total = r0 = 0;
+#pragma unroll
+                    for (int q = 0; q < kHeadIds; ++q) {
+                        const uint64_t m = wave_ballot(left != 0u);
+                        if (left != 0u) list[total + lanes_below(m)] = left0 + static_cast<uint32_t>(__builtin_ctz(left));
+                        left &= left - 1u;
+                        total += static_cast<uint32_t>(__popcll(m));
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                    continue;
+                } else if (asked < to_ask) {
+                    const uint32_t x = asked + static_cast<uint32_t>(lane);
+                    const bool mine = x < to_ask;
+                    const uint32_t g = who[mine ? x / many_words : 0u], word = x % many_words;
+                    const uint64_t w = poll_word(reread(ka)->more + 2 * groups +
+                                                     (mine ? (static_cast<int64_t>(par) * groups + g) * many_words + word : 0),
+                                                 mine, seq & kMoreTag, kMoreTag, &dead);
+                    left = mine ? static_cast<uint32_t>(w >> 32) : 0u;
+                    left0 = g * static_cast<uint32_t>(n_local) + word * 32u;
+                    asked += 64u;
+                    continue;
+                } else {
+                    break;
+                }
+                deliver_spikes(c, have, src, slot * static_cast<uint32_t>(n_local), t, flat);
+            }
+        }
+        if (dead) s_dead = 1u;
+        if (far) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // pushes into the ring are there before anyone goes on
+        lds_barrier();
+        if (s_dead != 0u) {
+            if (tid == 0) __hip_atomic_store(reread(ka)->fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            break;
+        }
+        // ---- vertex update
+        if (owns) {
+            const int got = __hip_atomic_exchange(c.slots + slot * static_cast<uint32_t>(n_local) + tid, 0, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+            const float in = static_cast<float>(got) * c.unit;
+            const bool spike = ((spk >> lane) & 1u) != 0u;
+            if (raster) {
+                *raster = spk;
+                raster += raster_words;
+            }
+            if (opaque(records) != 0u && valid) {
+                const const_args r = reread(ka);
+                if (r->rec_v) r->rec_v[static_cast<int64_t>(row) * n_total + j] = V;
+                if (r->rec_input) r->rec_input[static_cast<int64_t>(row) * n_total + j] = in;
+            }
+            float u = iext;
+            u = pulse ? u + p.drive_amp : u;
+            const float vn = V + p.decay * (p.v_rest - V) + in + u + noise;
+            const bool held = t - last - 1u < static_cast<uint32_t>(p.n_ref);
+            V = (spike | held) ? p.v_reset : vn;
+            prev = spike ? last : prev;
+            last = spike ? t : last;
+            bits = (bits & ~(1u << (t & 31u))) | ((spike ? 1u : 0u) << (t & 31u));
+            if (obs && valid) {
+                acc = acc + cal;
+                if (t0_64 + k + 1 == next_flush) {
+                    const const_args r = reread(ka);
+                    if (frame < r->frame_cap)
+                        r->frames[frame * c.n_pad + j] = static_cast<float>(acc / static_cast<double>(next_flush - frame_first));
+                    acc = 0.0;
+                }
+                cal = cal + p.dt_d * (-cal / p.tau_c_d + (spike ? 1.0 : 0.0));
+            }
+            if (pulls && (t & 31u) == 31u && valid) {
+                uint32_t* hist = reread(ka)->hist;
+                hist[static_cast<int64_t>((t & 0xFFu) >> 5) * c.n_pad + j] = bits;
+                bits = hist[static_cast<int64_t>(((t + 1u) & 0xFFu) >> 5) * c.n_pad + j];
+            }
+            if (late != 0.0f) {
+                const uint32_t to = slot == 0u ? W : slot - 1u;         // slot of step t + W
+                atomicAdd(c.slots + to * static_cast<uint32_t>(n_local) + tid, static_cast<int>(late * inv_unit));
+            }
+            spk = wave_ballot(valid && V >= p.v_th);
+        }
+        if (obs && t0_64 + k + 1 == next_flush) {
+            const const_args r = reread(ka);
+            ++frame;
+            frame_first = next_flush;
+            next_flush = ((frame + 1) * r->frame_den + r->frame_num - 1) / r->frame_num;
+        }
+        ++row;
+        slot = slot == W ? 0u : slot + 1u;
+        if (k + 1 < n_steps) publish(seq + 1u);
+    }
+    lds_barrier();
+
+    // ---- state out
+    a = reread(ka);
+    const uint32_t t1 = t0 + static_cast<uint32_t>(row);
+    for (uint32_t i = tid; i < W * quads; i += blockDim.x) {
+        const uint32_t k = i / quads, v = (i - k * quads) * 4u, s = slot + k > W ? slot + k - (W + 1u) : slot + k;
+        const int4 x = *reinterpret_cast<const int4*>(c.slots + s * static_cast<uint32_t>(n_local) + v);
+        if ((x.x | x.y | x.z | x.w) != 0)
+            *reinterpret_cast<float4*>(c.ring + static_cast<int64_t>((t1 + k) & c.ring_mask) * c.n_pad + v) =
+                make_float4(static_cast<float>(x.x) * c.unit, static_cast<float>(x.y) * c.unit, static_cast<float>(x.z) * c.unit,
+                            static_cast<float>(x.w) * c.unit);
+    }
+    if (valid) {
+        const uint32_t a1 = t1 - last, a2 = t1 - prev;
+        a->V[j] = V;
+        a->age[j] = static_cast<uint16_t>((a1 < 255u ? a1 : 255u) | ((a2 < 255u ? a2 : 255u) << 8));
+        if (pulls) a->hist[static_cast<int64_t>((t1 & 0xFFu) >> 5) * c.n_pad + j] = bits;
+        if (obs) {
+            a->calcium[j] = cal;
+            a->frame_acc[j] = acc;
+        }
+    }
+    if (pulls && owns) {
+        const uint64_t recent = wave_ballot(valid && t1 - last <= static_cast<uint32_t>(a->d_sum));
+        if (lane == 0 && j < c.n_pad) put_summary(a->summary, j, recent, a->sum_shift);
+    }
+}
+
+// The ring of arrival steps from pull delivery's spike history: every edge
+// adds its weight where its source fired in the last `delay` steps.
+struct RebuildArgs {
+    const int32_t* __restrict__ src;
+    const uint16_t* __restrict__ w;
+    const uint8_t* __restrict__ d;
+    const uint8_t* __restrict__ rowstart;
+    const int32_t* __restrict__ chunk_row0;
+    const uint16_t* __restrict__ age;
+    const uint32_t* __restrict__ hist;
+    float* ring;
+    int64_t n_chunks, n_pad;
+    uint32_t t, ring_mask;
+};
+
+// f(slot, its row) for the lane's eight slots of a chunk (a wave's).
+template <class F>
+__device__ __forceinline__ void each_slot(const uint8_t* rowstart, const int32_t* chunk_row0, int64_t chunk, F f) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t rs = rowstart[chunk * 64 + lane] & (lane == 0 ? ~1u : ~0u);    // (the first slot's row is chunk_row0)
+    uint32_t total;
+    int64_t r = chunk_row0[chunk] + wave_prefix(static_cast<uint32_t>(__popc(rs)), &total);
+    for (int k = 0; k < kEdgesPerLane; ++k) {
+        r += (rs >> k) & 1u;
+        f(chunk * kChunkEdges + lane * kEdgesPerLane + k, r);
+    }
+}
+
+__global__ void __launch_bounds__(256) rebuild_kernel(RebuildArgs a) {
+    const int64_t chunk = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (chunk >= a.n_chunks) return;
+    each_slot(a.rowstart, a.chunk_row0, chunk, [&](int64_t e, int64_t r) {
+        const uint32_t wb = a.w[e], d = a.d[e];
+        if ((wb & 0x7FFFu) == 0u) return;
+        const int64_t src = a.src[e];
+        if ((a.age[src] & 0xFFu) > d) return;
+        for (uint32_t back = 1; back <= d; ++back) {
+            const uint32_t ts = a.t - back;
+            if ((a.hist[static_cast<int64_t>((ts & 0xFFu) >> 5) * a.n_pad + src] >> (ts & 31u)) & 1u)
+                atomicAdd(a.ring + static_cast<int64_t>((ts + d) & a.ring_mask) * a.n_pad + r, half_bits_to_float(wb));
+        }
+    });
+}
+
+// The out-edge tables at net_build: count the lists' edges (kFill false: into
+// off[list + 2]), prefix sums, and fill them; off[list + 1] counts up while its
+// list is filled and opens the next list after.  The order within a list does
+// not matter.
+struct TableArgs {
+    const int32_t* __restrict__ src;
+    const uint16_t* __restrict__ w;
+    const uint8_t* __restrict__ d;
+    const uint8_t* __restrict__ rowstart;
+    const int32_t* __restrict__ chunk_row0;
+    uint32_t* off;
+    uint2* edge;
+    int64_t n_chunks, n_total;
+    int32_t n_local, set_groups, window, lg;
+};
+
+template <bool kFill>
+__global__ void __launch_bounds__(256) table_kernel(TableArgs a) {
+    const int64_t chunk = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (chunk >= a.n_chunks) return;
+    each_slot(a.rowstart, a.chunk_row0, chunk, [&](int64_t k, int64_t r) {
+        const uint32_t wb = a.w[k];
+        if ((wb & 0x7FFFu) == 0u) return;
+        const uint32_t g = static_cast<uint32_t>(r) / static_cast<uint32_t>(a.n_local), set = g / static_cast<uint32_t>(a.set_groups);
+        const int64_t list = (static_cast<int64_t>(set) * a.n_total + a.src[k]) * a.set_groups + (g - set * a.set_groups);
+        if (!kFill) {
+            atomicAdd(a.off + list + 2, 1u);
+            return;
+        }
+        const uint32_t local = static_cast<uint32_t>(r) - g * static_cast<uint32_t>(a.n_local), d = a.d[k];
+        const int e = static_cast<int>((wb >> 10) & 31u);
+        const int32_t units = static_cast<int32_t>((wb & 0x3FFu) | (e ? 0x400u : 0u)) << ((e > 1 ? e : 1) - 25 - a.lg);
+        a.edge[atomicAdd(a.off + list + 1, 1u)] =
+            make_uint2(static_cast<int>(d) <= a.window ? d * static_cast<uint32_t>(a.n_local) + local : kFar | d << 16 | local,
+                       static_cast<uint32_t>((wb & 0x8000u) ? -units : units));
+    });
+}
+
+// Inclusive prefix sums of x[n] in place: the sums of blocks of 4,096 values,
+// their prefix sums by one workgroup, the values of each block.
+constexpr int kScanBlock = 4096;
+__device__ __forceinline__ uint32_t block_prefix(uint32_t x, uint32_t* total) {      // 256 threads
+    __shared__ uint32_t sums[4];
+    const int wave = threadIdx.x >> 6;
+    uint32_t mine, before = 0, all = 0;
+    const uint32_t p = wave_prefix(x, &mine);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sums[wave] = mine;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        before += w < wave ? sums[w] : 0u;
+        all += sums[w];
+    }
+    *total = all;
+    return p + before;
+}
+
+__global__ void __launch_bounds__(256) scan_sums_kernel(const uint32_t* x, int64_t n, uint32_t* sums) {
+    const int64_t at = static_cast<int64_t>(blockIdx.x) * kScanBlock + threadIdx.x * 16;
+    uint32_t s = 0, total;
+    for (int k = 0; k < 16; ++k) s += at + k < n ? x[at + k] : 0u;
+    (void)block_prefix(s, &total);
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+__global__ void __launch_bounds__(256) scan_blocks_kernel(uint32_t* sums, int n) {
+    uint32_t base = 0;
+    for (int i0 = 0; i0 < n; i0 += 256) {
+        const int i = i0 + static_cast<int>(threadIdx.x);
+        const uint32_t x = i < n ? sums[i] : 0u;
+        uint32_t total;
+        const uint32_t before = block_prefix(x, &total);
+        if (i < n) sums[i] = base + before;
+        base += total;
+    }
+}
+
+__global__ void __launch_bounds__(256) scan_kernel(uint32_t* x, int64_t n, const uint32_t* sums) {
+    const int64_t at = static_cast<int64_t>(blockIdx.x) * kScanBlock + threadIdx.x * 16;
+    uint32_t v[16], s = 0, total;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        v[k] = at + k < n ? x[at + k] : 0u;
+        s += v[k];
+    }
+    uint32_t run = sums[blockIdx.x] + block_prefix(s, &total);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        run += v[k];
+        if (at + k < n) x[at + k] = run;
+    }
+}
+
+__global__ void __launch_bounds__(256) zero_kernel(float4* p, int64_t n) {
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * 256)
+        p[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+size_t run_lds_bytes(const ResidentPlan& r) {
+    return (static_cast<size_t>(r.window) + 1) * r.n_local * sizeof(int) + static_cast<size_t>(r.threads / 64) * kListWords * sizeof(uint32_t);
+}
+
+}  // namespace
+
+bool resident_fits(const ResidentPlan& r, int n_cu, size_t lds_max) {
+    const size_t lds = run_lds_bytes(r);
+    int per_cu = 0;
+    return lds + 1024 <= lds_max && r.groups <= r.threads &&
+           hipFuncSetAttribute(reinterpret_cast<const void*>(&run_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(lds_max - 1024)) == hipSuccess &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, run_kernel, r.threads, lds) == hipSuccess &&
+           per_cu >= 1 && r.groups <= n_cu;
+}
+
+// (`sums`: one word per 4,096 entries of the offsets)
+hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, uint32_t* off, int64_t n_off, uint2* edge, uint32_t* sums,
+                                  int lg, hipStream_t s) {
+    TableArgs a{g.src, g.w, g.d, g.rowstart, g.chunk_row0, off, edge, g.n_chunks, g.n_total, r.n_local, r.set_groups, r.window, lg};
+    const dim3 chunks(static_cast<unsigned>((g.n_chunks + 3) / 4)), blocks(static_cast<unsigned>((n_off + kScanBlock - 1) / kScanBlock));
+    table_kernel<false><<<chunks, dim3(256), 0, s>>>(a);
+    scan_sums_kernel<<<blocks, dim3(256), 0, s>>>(off, n_off, sums);
+    scan_blocks_kernel<<<dim3(1), dim3(256), 0, s>>>(sums, static_cast<int>(blocks.x));
+    scan_kernel<<<blocks, dim3(256), 0, s>>>(off, n_off, sums);
+    table_kernel<true><<<chunks, dim3(256), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+size_t resident_head_words(const ResidentPlan& r) { return 2 * static_cast<size_t>(r.groups) * kHeadStep; }
+
+hipError_t launch_resident_renumber(const ResidentPlan& r, hipStream_t s) {
+    zero_kernel<<<dim3(64), dim3(256), 0, s>>>(reinterpret_cast<float4*>(r.more), static_cast<int64_t>(r.groups) * (1 + r.n_local / 32));
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_rebuild(const DeviceGraph& g, const ResidentPlan& r, int64_t t, hipStream_t s) {
+    const int64_t n4 = (static_cast<int64_t>(r.ring_mask) + 1) * g.n_pad / 4;
+    zero_kernel<<<dim3(2048), dim3(256), 0, s>>>(reinterpret_cast<float4*>(r.ring), n4);
+    RebuildArgs a{g.src, g.w, g.d, g.rowstart, g.chunk_row0, g.age, g.ring, r.ring, g.n_chunks, g.n_pad,
+                  static_cast<uint32_t>(t), r.ring_mask};
+    rebuild_kernel<<<dim3(static_cast<unsigned>((g.n_chunks + 3) / 4)), dim3(256), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident(const DeviceGraph& g, const ResidentPlan& r, int64_t t0, int32_t n_steps, const net_record* rec,
+                           int32_t frame_num, int32_t frame_den, hipStream_t s) {
+    RunArgs a;
+    a.off = r.off;
+    a.edge = r.edge;
+    a.ring = r.ring;
+    a.head = r.head;
+    a.more = r.more;
+    a.fail = r.fail_dev;
+    a.V = g.V;
+    a.age = g.age;
+    a.hist = r.push ? nullptr : g.ring;
+    a.summary = r.push ? nullptr : g.summary;
+    a.drive_thr = g.drive_thr;
+    a.i_ext = g.i_ext;
+    a.calcium = (g.calcium && frame_num > 0) ? g.calcium : nullptr;
+    a.frame_acc = g.frame_acc;
+    a.frames = g.frames;
+    a.rec_raster = rec ? rec->raster : nullptr;
+    a.rec_v = rec ? rec->v : nullptr;
+    a.rec_input = rec ? rec->input : nullptr;
+    a.caller_of = g.caller_of;
+    a.t0 = t0;
+    a.n_total = g.n_total;
+    a.n_pad = g.n_pad;
+    a.raster_words = (g.n_total + 63) / 64;
+    a.ring_mask = r.ring_mask;
+    a.seq0 = r.seq;
+    a.n_steps = n_steps;
+    a.n_local = r.n_local;
+    a.set_groups = r.set_groups;
+    a.window = r.window;
+    a.max_delay = g.max_delay;
+    a.d_sum = g.d_sum;
+    a.sum_shift = g.sum_shift;
+    a.frame_cap = g.frame_cap;
+    a.frame_num = frame_num > 0 ? frame_num : 1;
+    a.frame_den = frame_den > 0 ? frame_den : 1;
+    a.unit = r.unit;
+    a.inv_unit = r.inv_unit;
+    a.params = g.params;
+    void* args[] = {&a};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&run_kernel), dim3(r.groups), dim3(r.threads), args,
+                                      static_cast<unsigned>(run_lds_bytes(r)), s);
+}
+
+}  // namespace geonet

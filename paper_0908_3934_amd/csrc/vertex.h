@@ -118,5 +118,81 @@ __device__ __forceinline__ void put_bits_shared(uint64_t* words, int64_t u0, uin
     }
 }
 
+// The wave's 64 bits of the recent-spike summary (first vertex j).
+__device__ __forceinline__ void put_summary(uint32_t* summary, int64_t j, uint64_t recent, int sum_shift) {
+    if (sum_shift == 0) {
+        reinterpret_cast<uint64_t*>(summary)[j >> 6] = recent;
+    } else {
+        // one bit per vertex pair: OR the pairs, then pack the even bits
+        uint64_t x = (recent | (recent >> 1)) & 0x5555555555555555ull;
+        x = (x | (x >> 1)) & 0x3333333333333333ull;
+        x = (x | (x >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+        x = (x | (x >> 4)) & 0x00FF00FF00FF00FFull;
+        x = (x | (x >> 8)) & 0x0000FFFF0000FFFFull;
+        x = (x | (x >> 16)) & 0x00000000FFFFFFFFull;
+        summary[j >> 6] = static_cast<uint32_t>(x);
+    }
+}
+
+// Barrier that orders LDS only (records on their way to memory are not waited for).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ uint64_t read_lane64(uint64_t v, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(v), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(v >> 32), lane);
+    return lo | (static_cast<uint64_t>(hi) << 32);
+}
+
+// Memory that no kernel writes while one reads it: uniform words of it are
+// scalar loads.
+typedef const uint32_t __attribute__((address_space(4)))* const_words;
+
+// A kernel's arguments, read again where they are used: a pointer the
+// compiler cannot see through keeps the dozens that only the start, the end or
+// a rare branch needs out of scalar registers while the steps run.
+template <class P>
+__device__ __forceinline__ P reread(P p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// A wave-uniform value that the compiler takes for a new one each time.
+__device__ __forceinline__ uint32_t opaque(uint32_t x) {
+    x = __builtin_amdgcn_readfirstlane(x);
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+// A struct in memory that no kernel writes, by scalar loads (`p` is uniform).
+template <class T>
+__device__ __forceinline__ T load_const(const T* p) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    const const_words w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(p));
+    uint32_t words[sizeof(T) / 4];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) words[i] = w[i];
+    T v;
+    __builtin_memcpy(&v, words, sizeof(T));
+    return v;
+}
+
+// Sum of x over the lanes below this one; *total over all (DPP row shifts and
+// row broadcasts).
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x, uint32_t* total) {
+    uint32_t s = x;
+    s += __builtin_amdgcn_update_dpp(0u, s, 0x111, 0xF, 0xF, false);   // row_shr:1
+    s += __builtin_amdgcn_update_dpp(0u, s, 0x112, 0xF, 0xF, false);   // row_shr:2
+    s += __builtin_amdgcn_update_dpp(0u, s, 0x114, 0xF, 0xF, false);   // row_shr:4
+    s += __builtin_amdgcn_update_dpp(0u, s, 0x118, 0xF, 0xF, false);   // row_shr:8
+    s += __builtin_amdgcn_update_dpp(0u, s, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+    s += __builtin_amdgcn_update_dpp(0u, s, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+    *total = __builtin_amdgcn_readlane(s, 63);
+    return s - x;
+}
+
 }  // namespace
 }  // namespace geonet
