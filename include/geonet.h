@@ -175,7 +175,7 @@ typedef struct {
                                              sum exact, runs calls of 8 steps or more, outside a timing
                                              window and not on a capturing stream, in one launch that keeps
                                              it resident on the chip.  Same results; 8 B per edge and 4 B
-                                             per vertex and 256 (from 32,768 vertices on 512) vertices of
+                                             per vertex and workgroup (64 vertices, or one per CU) of
                                              device memory more.) */
 #define NET_BUILD_DELIVER_UNROLL2 16      /* delivery: two 512-edge chunks per wave iteration
                                              (default one) */

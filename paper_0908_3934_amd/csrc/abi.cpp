@@ -435,10 +435,12 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
 // Shape and tables of the resident kernel for the handle's one network; left
 // disabled where it does not fit.
 //
-// Vertices per workgroup: 256, or 512 once those would be more than 128
-// workgroups (65,536 vertices, 128 steps: 256 each 522 us, 512 each 503 us,
-// 1,024 each 648 us; 8,192 vertices, 256 steps: 704, 748 and 1,080 us), beyond
-// 512 per CU as many as it takes, up to 1,024, the threads of a workgroup.
+// As many workgroups as there are CUs, of at least a wave's 64 vertices and up
+// to 1,024, the threads of a workgroup: the exchange is out of the way, and more
+// of them share a spike's edges (8,192 vertices, 256 steps: 64 each 477 us, 128
+// each 498, 256 each 526, 512 each 596; 65,536 vertices, 128 steps: 256 each 342
+// us, 512 each 383).  1,024 threads whatever their vertices, for the waves that
+// deliver (512: 481 and 354 us, 256: 493 and 381 us).
 net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     DeviceGraph& g = h->g;
     ResidentPlan r;
@@ -449,7 +451,7 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop || n_cu < 1)
         return NET_OK;
     const int64_t n = g.n_total;
-    r.n_local = static_cast<int>((std::max(std::min<int64_t>(std::max<int64_t>((n + 127) / 128, 256), 512), (n + n_cu - 1) / n_cu) + 63) / 64 * 64);
+    r.n_local = static_cast<int>(((n + n_cu - 1) / n_cu + 63) / 64 * 64);
     if (r.n_local > 1024 || hg.n_edges > (int64_t(1) << 28) || !(hg.row_abs_max < std::ldexp(1.0, 31 + hg.ulp_min)))
         return NET_OK;
     // sets of workgroups, one per XCD (the last groups may be left without vertices)
@@ -458,7 +460,7 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     const int sets = groups > kXcds && (groups + kXcds - 1) / kXcds * kXcds <= n_cu ? kXcds : 1;
     r.set_groups = (groups + sets - 1) / sets;
     r.groups = r.set_groups * sets;
-    r.threads = std::max(r.n_local, 512);
+    r.threads = 1024;
     const int64_t slots = (static_cast<int64_t>(lds_max) - 1024 - r.threads * 24) / (4 * r.n_local);   // (beside the waves' lists)
     r.window = static_cast<int>(std::min<int64_t>(hg.max_delay, slots - 1));
     if (r.window < 1 || !resident_fits(r, n_cu, static_cast<size_t>(lds_max))) return NET_OK;
@@ -480,7 +482,7 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     if (st == NET_OK) st = zeros(h, &dedge, static_cast<size_t>(std::max<int64_t>(hg.n_edges, 1)), s, "resident edges");
     if (st == NET_OK) st = zeros(h, &sums, n_off / 4096 + 1, s, "resident edges");
     if (st == NET_OK) st = zeros(h, &r.head, resident_head_words(r), s, "spike exchange");
-    if (st == NET_OK) st = zeros(h, &r.more, static_cast<size_t>(r.groups) * 2 * (1 + r.n_local / 32), s, "spike exchange");
+    if (st == NET_OK) st = zeros(h, &r.more, resident_more_words(r), s, "spike exchange");
     if (st == NET_OK && !h->lc.push) {
         r.ring_mask = ring_slots - 1;
         st = zeros(h, &r.ring, ring_words, s, "arrival ring");
@@ -669,7 +671,7 @@ net_status step_loop(net* h, int64_t n_steps, const net_record* rec, hipStream_t
 }
 
 // Whether a call of n_steps goes to the resident kernel.  Its launch costs
-// about 20 us more than a step's kernels (8 us to 13 us a step against 2 to 4):
+// about 20 us more than a step's kernels (6 to 13 us a step against 2 to 4):
 // calls below kResidentMinSteps stay with those, and where the ring of
 // arrivals has to be rebuilt first (about 100 us), calls below
 // kResidentMinRebuild.  A timing window times the step's kernels; a stream that

@@ -338,6 +338,7 @@ struct ResidentPlan {
 };
 bool resident_fits(const ResidentPlan& r, int n_cu, size_t lds_max);
 size_t resident_head_words(const ResidentPlan& r);
+size_t resident_more_words(const ResidentPlan& r);
 // Out-edge tables of the resident kernel from the handle's edges (off: zero; lg: the weights' unit is 2^lg).
 hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, uint32_t* off, int64_t n_off, uint2* edge, uint32_t* sums,
                                   int lg, hipStream_t s);

@@ -3,15 +3,17 @@
 // LDS) and the workgroups exchange each step's spikes through memory.
 //
 // Exchange.  A workgroup publishes its spikes of step t + 1 as soon as step t
-// has updated its vertices: a word with a tag of the step, their number and up to
-// four vertex indices; up to four more are in a second word, and where still more
-// fire, one tagged word per 32 vertices.
+// has updated its vertices, before it looks at the others' spikes of step t
+// (which step t + 1's input needs, but not step t's): a word with a tag of the
+// step, their number and up to four vertex indices; up to three more are in a
+// second word, and where still more fire, one tagged word per 32 vertices.
 // Every workgroup reads every other's word, again until its tag is the step's,
-// and the others as the number says.  A word is one 8-byte access, so it needs no order towards any other;
-// two sets in turn are enough, since a workgroup publishes t + 2 only after it
-// has read all words of t + 1, which their owners publish after reading all of
-// t.  The launch is cooperative (all workgroups are on the chip together), and
-// every wait has a limit, after which the launch ends and the handle fails.
+// and the others as the number says.  A word is one 8-byte access, so it needs
+// no order towards any other.  Four sets of words in turn are enough: a
+// workgroup publishes t + 2 after it has read all words of t, whose owners had
+// read all words of t - 2 before they published them.  The launch is
+// cooperative (all workgroups are on the chip together), and every wait has a
+// limit, after which the launch ends and the handle fails.
 //
 // Delivery.  Out-edges are kept by (set of workgroups, source, workgroup of the
 // target), so a workgroup finds its part of a spike's edges with one load of
@@ -40,6 +42,7 @@ constexpr int kHeadIds = 4, kMoreIds = 3;         // vertex indices in the first
 // workgroups: 1.12 us against 1.67 with 16 words a line; among 32, 0.99 against
 // 1.33).
 constexpr int kHeadStep = 16;
+constexpr int kSets = 4;                          // sets of words in turn (see above)
 constexpr uint32_t kMoreTag = 0x7FFFFFFFu;        // (a second word may stand for long: a long tag)
 constexpr int kListWords = 64 * kHeadIds + 128;   // a wave's list of spikes, of workgroups, and deliver_spikes' words
 constexpr uint32_t kHeadMany = 15u;               // its count where they do not fit
@@ -51,8 +54,8 @@ struct RunArgs {
     const uint2* __restrict__ edge;     // (delay n_local + target in the group, or for delays beyond the window kFar |
                                         // delay << 16 | target; weight in units)
     float* ring;                        // [ring_mask + 1][n_pad] arrivals by step
-    uint64_t* head;                     // [2][groups] first words, kHeadStep apart
-    uint64_t* more;                     // [2][groups] second words, then [2][groups][n_local / 32] words of spike bits
+    uint64_t* head;                     // [kSets][groups] first words, kHeadStep apart
+    uint64_t* more;                     // [kSets][groups] second words, then [kSets][groups][n_local / 32] words of spike bits
     uint32_t* fail;                     // host memory: set where a wait reached its limit
     float* __restrict__ V;
     uint16_t* __restrict__ age;
@@ -176,14 +179,16 @@ __device__ __forceinline__ void deliver_spikes(const RunCtx& c, bool have, uint3
     }
 }
 
-// What bounds it: the exchange (a word takes about 1 us from one workgroup to
-// all others at 8 workgroups, 2 us at 256) and the two dependent loads of the
-// spikes' edges; noise is drawn while the words are on their way.  us per step,
-// one launch or two per step before and now (noise 0.05, 3-D, about 100 in-edges
-// a vertex, 0.5 spikes a step and 1,000 vertices): 8,192 vertices 7.6 / 2.7;
-// 65,536 (pull delivery before) 13.0 / 3.9; 262,144 (push before) 6.5 / 4.8.
-// At the most spikes a network can have (one in 22 vertices a step) 8,192: 9.2 /
-// 6.8 (push before 7.4), 65,536: 30 / 19.5 (21), 262,144: 81 / 78.
+// What bounds it: the chain of a step, that is the look at the words, the two
+// dependent loads of the spikes' edges, the LDS adds, two barriers and the
+// update; at 1,024 vertices a CU also the noise (Philox and Box-Muller, 0.3 us a
+// wave).  us per step, the per-step kernels, this kernel with the spikes of step t
+// published and read within step t, and now (noise 0.05, 3-D, about 100 in-edges
+// a vertex, 0.5 spikes a step and 1,000 vertices): 8,192 vertices 7.6 / 2.7 /
+// 1.85; 65,536 (pull delivery before) 13.0 / 3.9 / 2.65; 262,144 (push before)
+// 6.5 / 4.8 / 4.2.  At the most spikes a network can have (one in 22 vertices a
+// step) 8,192: 9.2 / 6.8 / 4.1 (push 7.4), 65,536: 30 / 19.5 / 13.7 (21),
+// 262,144: (81) / 78 / 76.
 __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     extern __shared__ uint4 lds4[];
     __shared__ uint64_t s_words[2][16];
@@ -289,11 +294,11 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
 
     // this workgroup's spikes of the step whose sequence number is `seq`
     auto publish = [&](uint32_t seq) {
-        const uint32_t par = seq & 1u;
-        if (lane == 0 && owns) s_words[par][wave] = spk;
+        const uint32_t set_of = seq % kSets;
+        if (lane == 0 && owns) s_words[seq & 1u][wave] = spk;
         lds_barrier();
         if (wave != 0) return;
-        const uint64_t word = lane < own_words ? s_words[par][lane] : 0;
+        const uint64_t word = lane < own_words ? s_words[seq & 1u][lane] : 0;
         uint64_t some = wave_ballot(word != 0);
         uint64_t h0 = 0, h1 = 0;                                        // count from bit 16, indices from bits 20 and 31
         uint32_t n = 0;
@@ -311,44 +316,102 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
             uint64_t* const more = reread(ka)->more;
             if (n <= kHeadIds + kMoreIds) {
                 if (lane == 0)
-                    __hip_atomic_store(more + static_cast<int64_t>(par) * groups + b, h1 | (seq & kMoreTag), __ATOMIC_RELAXED,
+                    __hip_atomic_store(more + static_cast<int64_t>(set_of) * groups + b, h1 | (seq & kMoreTag), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             } else if (lane < own_words) {
-                uint64_t* to = more + 2 * groups + (static_cast<int64_t>(par) * groups + b) * (n_local >> 5) + 2 * lane;
+                uint64_t* to = more + kSets * groups + (static_cast<int64_t>(set_of) * groups + b) * (n_local >> 5) + 2 * lane;
                 __hip_atomic_store(to, word << 32 | (seq & kMoreTag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(to + 1, (word >> 32) << 32 | (seq & kMoreTag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         if (lane == 0)
-            __hip_atomic_store(head + (static_cast<int>(par) * groups + b) * kHeadStep, h0 | (seq & 0xFFFFu), __ATOMIC_RELAXED,
+            __hip_atomic_store(head + (static_cast<int>(set_of) * groups + b) * kHeadStep, h0 | (seq & 0xFFFFu), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     };
+    // control pulse and noise of step t0 + k
+    float noise = 0.0f;
+    bool pulse = false;
+    auto draw = [&](int32_t k) {
+        if (!draws) return;
+        const uint64_t t = static_cast<uint64_t>(t0_64 + k);
+        const uint4 r = philox4x32_10(make_uint4(jl, static_cast<uint32_t>(t), static_cast<uint32_t>(t >> 32), 0u),
+                                      opaque(p.key_lo), opaque(p.key_hi));
+        pulse = r.x < thr;
+        if (p.sigma != 0.0f) noise = p.sigma * gaussian(r.y, r.z);
+    };
+    draw(0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                    // the ring's entries taken over are cleared
     publish(seq0);
 
     int32_t row = 0;
     for (int32_t k = 0; k < n_steps; ++k) {
-        const uint32_t seq = seq0 + static_cast<uint32_t>(k), par = seq & 1u;
+        const uint32_t seq = seq0 + static_cast<uint32_t>(k), par = seq % kSets;
         const uint32_t t = t0 + static_cast<uint32_t>(k);
-        // the ring's arrivals of step t + W (no push reaches that step's entries any
-        // more) and the noise, drawn before the first look at the words: looking
-        // before they are there only delays them
-        float late = 0.0f, noise = 0.0f;
-        bool pulse = false;
-        if (far && valid)
-            late = __hip_atomic_exchange(c.ring + static_cast<int64_t>((t + W) & c.ring_mask) * c.n_pad + tid, 0.0f,
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (draws) {
-            const uint4 r = philox4x32_10(make_uint4(jl, t, static_cast<uint32_t>(static_cast<uint64_t>(t0_64 + k) >> 32), 0u),
-                                          opaque(p.key_lo), opaque(p.key_hi));
-            pulse = r.x < thr;
-            if (p.sigma != 0.0f) noise = p.sigma * gaussian(r.y, r.z);
+        // ---- vertex update
+        if (owns) {
+            const int got = __hip_atomic_exchange(c.slots + slot * static_cast<uint32_t>(n_local) + tid, 0, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+            const float in = static_cast<float>(got) * c.unit;
+            const bool spike = ((spk >> lane) & 1u) != 0u;
+            if (raster) {
+                *raster = spk;
+                raster += raster_words;
+            }
+            if (opaque(records) != 0u && valid) {
+                const const_args r = reread(ka);
+                if (r->rec_v) r->rec_v[static_cast<int64_t>(row) * n_total + j] = V;
+                if (r->rec_input) r->rec_input[static_cast<int64_t>(row) * n_total + j] = in;
+            }
+            float u = iext;
+            u = pulse ? u + p.drive_amp : u;
+            const float vn = V + p.decay * (p.v_rest - V) + in + u + noise;
+            const bool held = t - last - 1u < static_cast<uint32_t>(p.n_ref);
+            V = (spike | held) ? p.v_reset : vn;
+            prev = spike ? last : prev;
+            last = spike ? t : last;
+            bits = (bits & ~(1u << (t & 31u))) | ((spike ? 1u : 0u) << (t & 31u));
+            if (obs && valid) {
+                acc = acc + cal;
+                if (t0_64 + k + 1 == next_flush) {
+                    const const_args r = reread(ka);
+                    if (frame < r->frame_cap)
+                        r->frames[frame * c.n_pad + j] = static_cast<float>(acc / static_cast<double>(next_flush - frame_first));
+                    acc = 0.0;
+                }
+                cal = cal + p.dt_d * (-cal / p.tau_c_d + (spike ? 1.0 : 0.0));
+            }
+            if (pulls && (t & 31u) == 31u && valid) {
+                uint32_t* hist = reread(ka)->hist;
+                hist[static_cast<int64_t>((t & 0xFFu) >> 5) * c.n_pad + j] = bits;
+                bits = hist[static_cast<int64_t>(((t + 1u) & 0xFFu) >> 5) * c.n_pad + j];
+            }
+            spk = wave_ballot(valid && V >= p.v_th);
         }
-        // ---- every workgroup's spikes of the step
+        if (obs && t0_64 + k + 1 == next_flush) {
+            const const_args r = reread(ka);
+            ++frame;
+            frame_first = next_flush;
+            next_flush = ((frame + 1) * r->frame_den + r->frame_num - 1) / r->frame_num;
+        }
+        // the spikes of the next step are on their way while this step's are delivered
+        if (k + 1 < n_steps) publish(seq + 1u);
+        // ---- every workgroup's spikes of the step: published a step ago, so that
+        // the first look mostly finds them; meanwhile the next step's noise, and the
+        // ring's arrivals of step t + W (no push reaches that step's entries any more)
         bool dead = false;
+        float late = 0.0f;
         {
-            const uint64_t v = poll_word(head + (static_cast<int>(par) * groups + my_group) * kHeadStep, want, seq & 0xFFFFu,
-                                         0xFFFFu, &dead);
+            const uint64_t* const at = head + (static_cast<int>(par) * groups + my_group) * kHeadStep;
+            uint64_t v = want ? __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            if (far && valid)
+                late = __hip_atomic_exchange(c.ring + static_cast<int64_t>((t + W) & c.ring_mask) * c.n_pad + tid, 0.0f,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (k + 1 < n_steps) draw(k + 1);
+            const bool wait = want && (static_cast<uint32_t>(v) & 0xFFFFu) != (seq & 0xFFFFu);
+            if (wave_ballot(wait) != 0) {
+                const uint64_t got = poll_word(at, wait, seq & 0xFFFFu, 0xFFFFu, &dead);
+                v = wait ? got : v;
+            }
             const uint32_t n = want ? static_cast<uint32_t>(v >> 16) & 15u : 0u;
             const uint32_t base = static_cast<uint32_t>(my_group * n_local);
             uint32_t total = 0, r0 = 0;                     // the wave's spikes in its list, those delivered
@@ -410,7 +473,7 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
                     const uint32_t x = asked + static_cast<uint32_t>(lane);
                     const bool mine = x < to_ask;
                     const uint32_t g = who[mine ? x / many_words : 0u], word = x % many_words;
-                    const uint64_t w = poll_word(reread(ka)->more + 2 * groups +
+                    const uint64_t w = poll_word(reread(ka)->more + kSets * groups +
                                                      (mine ? (static_cast<int64_t>(par) * groups + g) * many_words + word : 0),
                                                  mine, seq & kMoreTag, kMoreTag, &dead);
                     left = mine ? static_cast<uint32_t>(w >> 32) : 0u;
@@ -423,66 +486,19 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
                 deliver_spikes(c, have, src, slot * static_cast<uint32_t>(n_local), t, flat);
             }
         }
+        if (late != 0.0f) {
+            const uint32_t to = slot == 0u ? W : slot - 1u;             // slot of step t + W
+            atomicAdd(c.slots + to * static_cast<uint32_t>(n_local) + tid, static_cast<int>(late * inv_unit));
+        }
         if (dead) s_dead = 1u;
         if (far) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // pushes into the ring are there before anyone goes on
         lds_barrier();
+        ++row;
+        slot = slot == W ? 0u : slot + 1u;
         if (s_dead != 0u) {
             if (tid == 0) __hip_atomic_store(reread(ka)->fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             break;
         }
-        // ---- vertex update
-        if (owns) {
-            const int got = __hip_atomic_exchange(c.slots + slot * static_cast<uint32_t>(n_local) + tid, 0, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-            const float in = static_cast<float>(got) * c.unit;
-            const bool spike = ((spk >> lane) & 1u) != 0u;
-            if (raster) {
-                *raster = spk;
-                raster += raster_words;
-            }
-            if (opaque(records) != 0u && valid) {
-                const const_args r = reread(ka);
-                if (r->rec_v) r->rec_v[static_cast<int64_t>(row) * n_total + j] = V;
-                if (r->rec_input) r->rec_input[static_cast<int64_t>(row) * n_total + j] = in;
-            }
-            float u = iext;
-            u = pulse ? u + p.drive_amp : u;
-            const float vn = V + p.decay * (p.v_rest - V) + in + u + noise;
-            const bool held = t - last - 1u < static_cast<uint32_t>(p.n_ref);
-            V = (spike | held) ? p.v_reset : vn;
-            prev = spike ? last : prev;
-            last = spike ? t : last;
-            bits = (bits & ~(1u << (t & 31u))) | ((spike ? 1u : 0u) << (t & 31u));
-            if (obs && valid) {
-                acc = acc + cal;
-                if (t0_64 + k + 1 == next_flush) {
-                    const const_args r = reread(ka);
-                    if (frame < r->frame_cap)
-                        r->frames[frame * c.n_pad + j] = static_cast<float>(acc / static_cast<double>(next_flush - frame_first));
-                    acc = 0.0;
-                }
-                cal = cal + p.dt_d * (-cal / p.tau_c_d + (spike ? 1.0 : 0.0));
-            }
-            if (pulls && (t & 31u) == 31u && valid) {
-                uint32_t* hist = reread(ka)->hist;
-                hist[static_cast<int64_t>((t & 0xFFu) >> 5) * c.n_pad + j] = bits;
-                bits = hist[static_cast<int64_t>(((t + 1u) & 0xFFu) >> 5) * c.n_pad + j];
-            }
-            if (late != 0.0f) {
-                const uint32_t to = slot == 0u ? W : slot - 1u;         // slot of step t + W
-                atomicAdd(c.slots + to * static_cast<uint32_t>(n_local) + tid, static_cast<int>(late * inv_unit));
-            }
-            spk = wave_ballot(valid && V >= p.v_th);
-        }
-        if (obs && t0_64 + k + 1 == next_flush) {
-            const const_args r = reread(ka);
-            ++frame;
-            frame_first = next_flush;
-            next_flush = ((frame + 1) * r->frame_den + r->frame_num - 1) / r->frame_num;
-        }
-        ++row;
-        slot = slot == W ? 0u : slot + 1u;
-        if (k + 1 < n_steps) publish(seq + 1u);
     }
     lds_barrier();
 
@@ -684,10 +700,11 @@ hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, u
     return hipGetLastError();
 }
 
-size_t resident_head_words(const ResidentPlan& r) { return 2 * static_cast<size_t>(r.groups) * kHeadStep; }
+size_t resident_head_words(const ResidentPlan& r) { return static_cast<size_t>(kSets) * r.groups * kHeadStep; }
+size_t resident_more_words(const ResidentPlan& r) { return static_cast<size_t>(kSets) * r.groups * (1 + r.n_local / 32); }
 
 hipError_t launch_resident_renumber(const ResidentPlan& r, hipStream_t s) {
-    zero_kernel<<<dim3(64), dim3(256), 0, s>>>(reinterpret_cast<float4*>(r.more), static_cast<int64_t>(r.groups) * (1 + r.n_local / 32));
+    zero_kernel<<<dim3(64), dim3(256), 0, s>>>(reinterpret_cast<float4*>(r.more), static_cast<int64_t>(kSets / 2) * r.groups * (1 + r.n_local / 32));
     return hipGetLastError();
 }
 
