@@ -172,7 +172,8 @@ typedef struct {
                                              kernels for every call.  (Otherwise one LIF network of up to
                                              1,024 vertices per CU, built with none of the delivery flags
                                              below but FUSED_STEP, PUSH, REORDER or AUTOTUNE and with every
-                                             sum exact, runs calls of 8 steps or more, outside a timing
+                                             sum exact, or plastic with its delays' arrivals in LDS,
+                                             runs calls of 8 steps or more, outside a timing
                                              window and not on a capturing stream, in one launch that keeps
                                              it resident on the chip.  Same results; 8 B per edge and 4 B
                                              per vertex and workgroup (64 vertices, or one per CU) of

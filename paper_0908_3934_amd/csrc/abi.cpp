@@ -452,8 +452,12 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
         return NET_OK;
     const int64_t n = g.n_total;
     r.n_local = static_cast<int>(((n + n_cu - 1) / n_cu + 63) / 64 * 64);
-    if (r.n_local > 1024 || hg.n_edges > (int64_t(1) << 28) || !(hg.row_abs_max < std::ldexp(1.0, 31 + hg.ulp_min)))
+    r.plastic = hg.plastic;
+    if (r.n_local > 1024 || hg.n_edges > (int64_t(1) << 28) ||
+        !(hg.plastic || hg.row_abs_max < std::ldexp(1.0, 31 + hg.ulp_min)))
         return NET_OK;
+    // (a plastic network's slots name source and target in 16 and 8 bits)
+    if (r.plastic && (n >= 65536 || r.n_local > 256)) return NET_OK;
     // sets of workgroups, one per XCD (the last groups may be left without vertices)
     constexpr int kXcds = 8;
     const int groups = static_cast<int>((n + r.n_local - 1) / r.n_local);
@@ -461,8 +465,16 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     r.set_groups = (groups + sets - 1) / sets;
     r.groups = r.set_groups * sets;
     r.threads = 1024;
+    if (r.plastic) {
+        // all delays have to fit: a bit per slot of the group and step, a word per thread
+        int64_t most = 1;
+        for (int64_t j = 0; j < n; j += r.n_local)
+            most = std::max<int64_t>(most, hg.row_first[std::min(j + r.n_local, n)] - hg.row_first[j]);
+        r.words = static_cast<int>((most + 31) / 32);
+        if (r.words > r.threads) return NET_OK;
+    }
     const int64_t slots = (static_cast<int64_t>(lds_max) - 1024 - r.threads * 24) / (4 * r.n_local);   // (beside the waves' lists)
-    r.window = static_cast<int>(std::min<int64_t>(hg.max_delay, slots - 1));
+    r.window = r.plastic ? hg.max_delay : static_cast<int>(std::min<int64_t>(hg.max_delay, slots - 1));
     if (r.window < 1 || !resident_fits(r, n_cu, static_cast<size_t>(lds_max))) return NET_OK;
     r.unit = std::ldexp(1.0f, hg.ulp_min);
     r.inv_unit = std::ldexp(1.0f, -hg.ulp_min);
@@ -471,10 +483,10 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     const size_t n_off = static_cast<size_t>(sets) * static_cast<size_t>(n * r.set_groups) + 2;
     uint32_t ring_slots = 1;
     while (ring_slots <= static_cast<uint32_t>(hg.max_delay)) ring_slots <<= 1;
-    const size_t ring_words = h->lc.push ? 0 : static_cast<size_t>(ring_slots) * static_cast<size_t>(g.n_pad);
+    const size_t ring_words = h->lc.push || r.plastic ? 0 : static_cast<size_t>(ring_slots) * static_cast<size_t>(g.n_pad);
     size_t mem_free = 0, mem_total = 0;
     if (hipMemGetInfo(&mem_free, &mem_total) != hipSuccess ||
-        2 * (4 * n_off + 8 * static_cast<size_t>(hg.n_edges) + 4 * ring_words) > mem_free)
+        2 * (4 * n_off + 8 * static_cast<size_t>(hg.n_edges) + 4 * (ring_words + (r.plastic ? hg.e_slots : 0))) > mem_free)
         return NET_OK;
     uint32_t *doff = nullptr, *sums = nullptr;
     uint2* dedge = nullptr;
@@ -483,7 +495,8 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     if (st == NET_OK) st = zeros(h, &sums, n_off / 4096 + 1, s, "resident edges");
     if (st == NET_OK) st = zeros(h, &r.head, resident_head_words(r), s, "spike exchange");
     if (st == NET_OK) st = zeros(h, &r.more, resident_more_words(r), s, "spike exchange");
-    if (st == NET_OK && !h->lc.push) {
+    if (st == NET_OK && r.plastic) st = zeros(h, &r.info, static_cast<size_t>(hg.e_slots), s, "resident edges");
+    if (st == NET_OK && ring_words != 0) {
         r.ring_mask = ring_slots - 1;
         st = zeros(h, &r.ring, ring_words, s, "arrival ring");
     }
@@ -630,7 +643,8 @@ net_status records_to_caller(net* h, const net_record* rec, int64_t rows, hipStr
 // The per-step kernels for n_steps steps (records optional), then the
 // step counter and the records' numbering.
 net_status step_loop(net* h, int64_t n_steps, const net_record* rec, hipStream_t s, bool observe) {
-    if (n_steps > 0) h->resident.valid = h->resident.push;   // (pull delivery leaves the arrivals' ring behind)
+    // (pull delivery leaves the arrivals' ring behind)
+    if (n_steps > 0) h->resident.valid = h->resident.push || h->resident.plastic;
     for (int64_t k = 0; k < n_steps; ++k) {
         const int64_t t = h->t + k;
         hipEvent_t d0 = nullptr, d1 = nullptr, u0, u1;
@@ -990,7 +1004,8 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
         if ((st = upload(h, &wq, hg.wq, hg.wq.size(), s, "plastic weights")) != NET_OK) return bail(st);
         if ((st = upload(h, &so, hg.slot_orig, hg.slot_orig.size(), s, "edge order")) != NET_OK) return bail(st);
         if ((st = upload(h, &rf, hg.row_first, hg.row_first.size(), s, "rows")) != NET_OK) return bail(st);
-        if ((st = zeros(h, &g.spk_hist, np * kStdpHist, s, "spike times")) != NET_OK) return bail(st);
+        if ((st = zeros(h, &g.spk_hist, np * kStdpHist, s, "spike times", 0x7F)) != NET_OK)   // (no spike: later than any step)
+             return bail(st);
         if ((st = zeros(h, &g.spk_cnt, np, s, "spike counts")) != NET_OK) return bail(st);
         g.wq = wq;
         g.slot_orig = so;
@@ -1421,7 +1436,7 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
     constexpr int kChosen = NET_BUILD_NO_LDS_SUMMARY | NET_BUILD_DELIVER_STREAM_WEIGHTS | NET_BUILD_DELIVER_NONTEMPORAL |
                             NET_BUILD_PER_STEP | NET_BUILD_DELIVER_UNROLL2 | NET_BUILD_DELIVER_PIPELINE | NET_BUILD_SUMMARY_HALF |
                             NET_BUILD_DELIVER_COMPACT | NET_BUILD_DELIVER_PACKED | NET_BUILD_GRAPH;
-    if (n_nets == 1 && !h->plan.enabled && !hg.plastic && !hg.any_izh && !hg.any_hh && hg.exact && !(bflags & kChosen) &&
+    if (n_nets == 1 && !h->plan.enabled && !hg.any_izh && !hg.any_hh && (hg.exact || hg.plastic) && !(bflags & kChosen) &&
         !(opts && (opts->block_threads || opts->blocks_per_cu)) && (frame_cap == 0 || hg.frame_num > 0) &&
         (st = plan_resident(h, hg, s)) != NET_OK)
         return bail(st);

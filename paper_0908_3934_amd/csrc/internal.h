@@ -321,6 +321,9 @@ constexpr uint32_t kResidentFar = 0x80000000u;
 struct ResidentPlan {
     bool enabled = false;
     bool push = false;              // its ring is the push delivery's (else its own, see `valid`)
+    bool plastic = false;           // a plastic network: arrivals as a bit per edge, made anew from the spikes at each call
+    int words = 0;                  // its words of a step's arrivals
+    uint32_t* info = nullptr;       // its slots (see RunArgs)
     bool valid = false;             // the ring holds the arrivals to come (pull delivery keeps spikes instead)
     int groups = 0, set_groups = 0, threads = 0;   // workgroups, those of a set, and their threads
     int n_local = 0;                // vertices per workgroup

@@ -47,6 +47,7 @@ constexpr uint32_t kMoreTag = 0x7FFFFFFFu;        // (a second word may stand fo
 constexpr int kListWords = 64 * kHeadIds + 128;   // a wave's list of spikes, of workgroups, and deliver_spikes' words
 constexpr uint32_t kHeadMany = 15u;               // its count where they do not fit
 constexpr uint32_t kFar = kResidentFar;
+constexpr uint32_t kNoEdge = 0xFFFFFFFFu;
 constexpr uint32_t kSpinLimit = 1u << 22;         // polls (a few seconds)
 
 struct RunArgs {
@@ -71,8 +72,18 @@ struct RunArgs {
     float* __restrict__ rec_input;
     const int32_t* __restrict__ caller_of;
     const NetParams* __restrict__ params;
+    // plastic networks (else null): per slot source | delay << 16 | target in its
+    // group << 24 (kNoEdge: none), weights in 2^-20, each row's first slot, the
+    // last kStdpHist spike steps of every vertex (kNoSpike: none) and their count
+    const uint32_t* __restrict__ info;
+    int32_t* wq;
+    const int32_t* __restrict__ row_first;
+    int32_t* spk_hist;
+    int32_t* spk_cnt;
+    double dt, alpha, beta;
     int64_t t0, n_total, n_pad, raster_words;
     uint32_t ring_mask, seq0;
+    int32_t words;                      // of a step's arrivals, a bit per slot of the group
     int32_t n_steps, n_local, set_groups, window, max_delay, d_sum, sum_shift, frame_cap, frame_num, frame_den;
     float unit, inv_unit;
 };
@@ -113,9 +124,16 @@ struct RunCtx {
     float unit;
 };
 
-// `now`: slot of step t x n_local
+// `now`: slot of step t x the slot's size (n_local, or the bits of its words)
+template <bool kPlastic>
 __device__ __forceinline__ void add_edge(const RunCtx& c, uint2 e, uint32_t now, uint32_t t) {
-    if (!(e.x & kFar)) {
+    if constexpr (kPlastic) {
+        // the edge's bit in its arrival step's words
+        uint32_t at = now + e.x;
+        at = at < at - c.size ? at : at - c.size;
+        atomicOr(reinterpret_cast<uint32_t*>(c.slots) + (at >> 5), 1u << (at & 31u));
+        (void)t;
+    } else if (!(e.x & kFar)) {
         const uint32_t at = now + e.x;
         atomicAdd(c.slots + (at < at - c.size ? at : at - c.size), static_cast<int>(e.y));
     } else {
@@ -126,12 +144,32 @@ __device__ __forceinline__ void add_edge(const RunCtx& c, uint2 e, uint32_t now,
     }
 }
 
+// Time since vertex i's last spike before step u (0 for u <= 0, u dt before any
+// spike).  Its owner may be adding spikes of steps near t, which are not before
+// u, in place of ones too old to be asked for.
+__device__ __forceinline__ double since_spike(const int32_t* hist, int64_t i, int64_t u, double dt) {
+    if (u <= 0) return 0.0;
+    const uint64_t* h = reinterpret_cast<const uint64_t*>(hist + i * kStdpHist);
+    uint64_t two[kStdpHist / 2];
+#pragma unroll
+    for (int q = 0; q < kStdpHist / 2; ++q) two[q] = __hip_atomic_load(h + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int64_t best = -1;
+#pragma unroll
+    for (int q = 0; q < kStdpHist / 2; ++q) {
+        const int64_t a = static_cast<int32_t>(two[q]), b = static_cast<int32_t>(two[q] >> 32);
+        best = a < u && a > best ? a : best;
+        best = b < u && b > best ? b : best;
+    }
+    return best < 0 ? static_cast<double>(u) * dt : static_cast<double>(u - best - 1) * dt;
+}
+
 // Delivers this workgroup's part of up to 64 spikes, one per lane (`have`).
 // Most have no edge here or a few: the edges of all lists are numbered through,
 // and the wave takes 64 of them at a time, four such loads in flight (`flat`:
 // 64 words of the wave's own).  With a lane per list up to four edges long and
 // the wave per longer one, a step of 262,144 vertices with 11,750 spikes took
 // 87 us, now 78 (65,536 vertices with 2,890 spikes: 25.3 and 19.5).
+template <bool kPlastic>
 __device__ __forceinline__ void deliver_spikes(const RunCtx& c, bool have, uint32_t src, uint32_t now, uint32_t t, uint32_t* flat) {
     constexpr int kLoads = 4;
     uint32_t e0 = 0u, len = 0u;
@@ -174,7 +212,7 @@ __device__ __forceinline__ void deliver_spikes(const RunCtx& c, bool have, uint3
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
             if (n0 + 64u * q >= total) break;
-            if (rec[q].y != 0u) add_edge(c, rec[q], now, t);
+            if (rec[q].y != 0u) add_edge<kPlastic>(c, rec[q], now, t);
         }
     }
 }
@@ -189,6 +227,15 @@ __device__ __forceinline__ void deliver_spikes(const RunCtx& c, bool have, uint3
 // 6.5 / 4.8 / 4.2.  At the most spikes a network can have (one in 22 vertices a
 // step) 8,192: 9.2 / 6.8 / 4.1 (push 7.4), 65,536: 30 / 19.5 / 13.7 (21),
 // 262,144: (81) / 78 / 76.
+//
+// kPlastic: a weight counts as it is when its edge's spike arrives, so a spike
+// sets a bit per edge in the words of its arrival step (LDS holds all steps up to
+// the largest delay), and step t adds the weights of its bits as integers and
+// then, the others' words on their way, updates them and the in-edges of the
+// vertices that fire: work per step for the arrivals and spikes instead of every
+// edge.  16,384 vertices, 1.2e6 edges: 16.7 us a step with a kernel over all
+// edges and one over all vertices, now 3.9.
+template <bool kPlastic>
 __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     extern __shared__ uint4 lds4[];
     __shared__ uint64_t s_words[2][16];
@@ -214,11 +261,18 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     c.slots = reinterpret_cast<int*>(lds4);
     c.n_pad = a->n_pad;
     c.ring_mask = a->ring_mask;
-    c.size = (W + 1u) * static_cast<uint32_t>(n_local);
+    const uint32_t slot_words = kPlastic ? static_cast<uint32_t>(a->words) : static_cast<uint32_t>(n_local);
+    const uint32_t slot_size = kPlastic ? slot_words * 32u : slot_words;
+    c.size = (W + 1u) * slot_size;
     c.lane = lane;
     c.unit = a->unit;
     const float inv_unit = a->inv_unit;
-    uint32_t* list = reinterpret_cast<uint32_t*>(c.slots + (W + 1u) * static_cast<uint32_t>(n_local)) + wave * kListWords;
+    uint32_t* const lists = reinterpret_cast<uint32_t*>(c.slots + (((W + 1u) * slot_words + 1u) & ~1u));
+    uint32_t* list = lists + wave * kListWords;
+    // plastic networks: the step's input sums, and each vertex's last spike before the step (-1: none)
+    unsigned long long* const sums = reinterpret_cast<unsigned long long*>(lists + waves * kListWords);
+    int32_t* const tlast = reinterpret_cast<int32_t*>(sums + n_local);
+    const int64_t first_slot = kPlastic ? a->row_first[j0 < n_total ? j0 : n_total] : 0;
     uint32_t *who = list + 64 * kHeadIds, *flat = who + 64;
     const uint32_t many_words = static_cast<uint32_t>(n_local) >> 5;
     const int64_t t0_64 = a->t0;
@@ -229,7 +283,7 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     if (tid == 0) s_dead = 0u;
     const uint32_t slot0 = static_cast<uint32_t>(static_cast<uint64_t>(t0_64) % (W + 1u));
     const uint32_t quads = static_cast<uint32_t>(n_local) >> 2;         // (four vertices at a time, four such loads in flight)
-    for (uint32_t i0 = tid; i0 < (W + 1u) * quads; i0 += 4u * blockDim.x) {
+    for (uint32_t i0 = tid; !kPlastic && i0 < (W + 1u) * quads; i0 += 4u * blockDim.x) {
         float4 x[4];
         float4* at[4];
 #pragma unroll
@@ -248,6 +302,24 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
             *reinterpret_cast<int4*>(c.slots + s * static_cast<uint32_t>(n_local) + v) =
                 make_int4(static_cast<int>(x[q].x * inv_unit), static_cast<int>(x[q].y * inv_unit),
                           static_cast<int>(x[q].z * inv_unit), static_cast<int>(x[q].w * inv_unit));
+        }
+    }
+    if constexpr (kPlastic) {
+        // the arrivals to come, from the spikes of the last steps
+        for (uint32_t i = tid; i < (W + 1u) * slot_words; i += blockDim.x) c.slots[i] = 0;
+        if (tid < n_local) sums[tid] = 0u;
+        lds_barrier();
+        const int64_t slots_here = a->row_first[j0 + n_local < n_total ? j0 + n_local : n_total] - first_slot;
+        for (int64_t rel = tid; rel < slots_here; rel += blockDim.x) {
+            const uint32_t info = a->info[first_slot + rel];
+            if (info == kNoEdge) continue;
+            const uint32_t src = info & 0xFFFFu, d = (info >> 16) & 0xFFu;
+            if ((a->age[src] & 0xFFu) > d) continue;
+            for (uint32_t back = 1; back <= d; ++back) {
+                const uint32_t ts = t0 - back;
+                if (!((a->hist[static_cast<int64_t>((ts & 0xFFu) >> 5) * c.n_pad + src] >> (ts & 31u)) & 1u)) continue;
+                add_edge<true>(c, make_uint2((d - back) * slot_size + static_cast<uint32_t>(rel), 1u), slot0 * slot_size, 0u);
+            }
         }
     }
     // (255 or more steps back: as good as never)
@@ -269,6 +341,14 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
         if (obs) {
             cal = a->calcium[j];
             acc = a->frame_acc[j];
+        }
+    }
+    int32_t last_at = -1, count = 0;                                    // plastic networks: the last spike's step, spikes so far
+    if (kPlastic && valid) {
+        count = a->spk_cnt[j];
+        for (int q = 0; q < kStdpHist && q < count; ++q) {
+            const int32_t ts = a->spk_hist[j * kStdpHist + q];
+            last_at = ts > last_at ? ts : last_at;
         }
     }
     uint64_t spk = wave_ballot(valid && V >= p.v_th);                   // this wave's spikes of the step to come
@@ -347,11 +427,31 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     for (int32_t k = 0; k < n_steps; ++k) {
         const uint32_t seq = seq0 + static_cast<uint32_t>(k), par = seq % kSets;
         const uint32_t t = t0 + static_cast<uint32_t>(k);
+        // ---- plastic networks: the weights of this step's arrivals
+        uint32_t arrived = 0u;
+        if constexpr (kPlastic) {
+            if (static_cast<uint32_t>(tid) < slot_words)
+                arrived = __hip_atomic_exchange(reinterpret_cast<uint32_t*>(c.slots) + slot * slot_words + tid, 0u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+            const const_args r = reread(ka);
+            for (uint32_t m = arrived; m != 0u; m &= m - 1u) {
+                const int64_t e = first_slot + tid * 32 + __builtin_ctz(m);
+                atomicAdd(sums + (r->info[e] >> 24), static_cast<unsigned long long>(static_cast<long long>(r->wq[e])));
+            }
+            lds_barrier();
+        }
         // ---- vertex update
         if (owns) {
+            float in;
+            if constexpr (kPlastic) {
+                const long long got = static_cast<long long>(__hip_atomic_exchange(sums + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                in = static_cast<float>(static_cast<double>(got) * (1.0 / 1048576.0));
+                tlast[tid] = last_at;
+            } else {
             const int got = __hip_atomic_exchange(c.slots + slot * static_cast<uint32_t>(n_local) + tid, 0, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            const float in = static_cast<float>(got) * c.unit;
+            in = static_cast<float>(got) * c.unit;
+            }
             const bool spike = ((spk >> lane) & 1u) != 0u;
             if (raster) {
                 *raster = spk;
@@ -385,6 +485,19 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
                 hist[static_cast<int64_t>((t & 0xFFu) >> 5) * c.n_pad + j] = bits;
                 bits = hist[static_cast<int64_t>(((t + 1u) & 0xFFu) >> 5) * c.n_pad + j];
             }
+            if constexpr (kPlastic) {
+                if (spk != 0) {
+                    if (spike) {
+                        const const_args r = reread(ka);
+                        __hip_atomic_store(r->spk_hist + j * kStdpHist + (count % kStdpHist), static_cast<int32_t>(t), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        r->spk_cnt[j] = ++count;
+                        last_at = static_cast<int32_t>(t);
+                    }
+                    // there before the next words go out: who has read those finds it
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                }
+            }
             spk = wave_ballot(valid && V >= p.v_th);
         }
         if (obs && t0_64 + k + 1 == next_flush) {
@@ -395,6 +508,38 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
         }
         // the spikes of the next step are on their way while this step's are delivered
         if (k + 1 < n_steps) publish(seq + 1u);
+        else if (kPlastic) lds_barrier();                               // (tlast)
+        // ---- plastic networks: the edges whose spike arrived or whose target fired
+        if constexpr (kPlastic) {
+            const const_args r = reread(ka);
+            const int64_t now = t0_64 + k;
+            auto learn = [&](int64_t e, uint32_t info) {
+                const uint32_t to = info >> 24;
+                const int32_t tl = tlast[to], w = r->wq[e];
+                const double since = now <= 0 ? 0.0 : (tl < 0 ? static_cast<double>(now) * r->dt : static_cast<double>(now - tl - 1) * r->dt);
+                const double q = since_spike(r->spk_hist, info & 0xFFFFu, now - ((info >> 16) & 0xFFu), r->dt) - since;
+                const double sg = q > 0.0 ? 1.0 : (q < 0.0 ? -1.0 : 0.0);
+                const double dw = r->dt * r->alpha * sg * exp(-r->beta * fabs(q));
+                r->wq[e] = w + static_cast<int32_t>(rint(dw * 1048576.0));
+            };
+            const uint64_t* const fired = s_words[seq & 1u];
+            for (uint32_t m = arrived; m != 0u; m &= m - 1u) {
+                const int64_t e = first_slot + tid * 32 + __builtin_ctz(m);
+                const uint32_t info = r->info[e], to = info >> 24;
+                if (!((fired[to >> 6] >> (to & 63u)) & 1u)) learn(e, info);       // (else with all of its target's below)
+            }
+            int turn = 0;
+            for (int x = 0; x < own_words; ++x) {
+                for (uint64_t m = read_lane64(fired[x], 0); m != 0; m &= m - 1) {
+                    if (turn++ % waves != wave) continue;
+                    const int64_t to = j0 + x * 64 + __builtin_ctzll(m), e1 = r->row_first[to + 1];
+                    for (int64_t e = r->row_first[to] + lane; e < e1; e += 64) {
+                        const uint32_t info = r->info[e];
+                        if (info != kNoEdge) learn(e, info);
+                    }
+                }
+            }
+        }
         // ---- every workgroup's spikes of the step: published a step ago, so that
         // the first look mostly finds them; meanwhile the next step's noise, and the
         // ring's arrivals of step t + W (no push reaches that step's entries any more)
@@ -483,7 +628,7 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
                 } else {
                     break;
                 }
-                deliver_spikes(c, have, src, slot * static_cast<uint32_t>(n_local), t, flat);
+                deliver_spikes<kPlastic>(c, have, src, slot * slot_size, t, flat);
             }
         }
         if (late != 0.0f) {
@@ -491,7 +636,8 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
             atomicAdd(c.slots + to * static_cast<uint32_t>(n_local) + tid, static_cast<int>(late * inv_unit));
         }
         if (dead) s_dead = 1u;
-        if (far) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // pushes into the ring are there before anyone goes on
+        // pushes into the ring, and weights, are there before anyone goes on
+        if (far || kPlastic) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lds_barrier();
         ++row;
         slot = slot == W ? 0u : slot + 1u;
@@ -505,7 +651,7 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     // ---- state out
     a = reread(ka);
     const uint32_t t1 = t0 + static_cast<uint32_t>(row);
-    for (uint32_t i = tid; i < W * quads; i += blockDim.x) {
+    for (uint32_t i = tid; !kPlastic && i < W * quads; i += blockDim.x) {
         const uint32_t k = i / quads, v = (i - k * quads) * 4u, s = slot + k > W ? slot + k - (W + 1u) : slot + k;
         const int4 x = *reinterpret_cast<const int4*>(c.slots + s * static_cast<uint32_t>(n_local) + v);
         if ((x.x | x.y | x.z | x.w) != 0)
@@ -585,8 +731,11 @@ struct TableArgs {
     const int32_t* __restrict__ chunk_row0;
     uint32_t* off;
     uint2* edge;
+    const int32_t* slot_orig;           // plastic networks (else null)
+    const int32_t* row_first;
+    uint32_t* info;
     int64_t n_chunks, n_total;
-    int32_t n_local, set_groups, window, lg;
+    int32_t n_local, set_groups, window, lg, words;
 };
 
 template <bool kFill>
@@ -595,7 +744,12 @@ __global__ void __launch_bounds__(256) table_kernel(TableArgs a) {
     if (chunk >= a.n_chunks) return;
     each_slot(a.rowstart, a.chunk_row0, chunk, [&](int64_t k, int64_t r) {
         const uint32_t wb = a.w[k];
-        if ((wb & 0x7FFFu) == 0u) return;
+        if (a.slot_orig) {
+            if (kFill) a.info[k] = kNoEdge;
+            if (a.slot_orig[k] < 0) return;
+        } else if ((wb & 0x7FFFu) == 0u) {
+            return;
+        }
         const uint32_t g = static_cast<uint32_t>(r) / static_cast<uint32_t>(a.n_local), set = g / static_cast<uint32_t>(a.set_groups);
         const int64_t list = (static_cast<int64_t>(set) * a.n_total + a.src[k]) * a.set_groups + (g - set * a.set_groups);
         if (!kFill) {
@@ -603,6 +757,12 @@ __global__ void __launch_bounds__(256) table_kernel(TableArgs a) {
             return;
         }
         const uint32_t local = static_cast<uint32_t>(r) - g * static_cast<uint32_t>(a.n_local), d = a.d[k];
+        if (a.slot_orig) {
+            const uint32_t rel = static_cast<uint32_t>(k - a.row_first[static_cast<int64_t>(g) * a.n_local]);
+            a.info[k] = static_cast<uint32_t>(a.src[k]) | d << 16 | local << 24;
+            a.edge[atomicAdd(a.off + list + 1, 1u)] = make_uint2(d * static_cast<uint32_t>(a.words) * 32u + rel, 1u);
+            return;
+        }
         const int e = static_cast<int>((wb >> 10) & 31u);
         const int32_t units = static_cast<int32_t>((wb & 0x3FFu) | (e ? 0x400u : 0u)) << ((e > 1 ? e : 1) - 25 - a.lg);
         a.edge[atomicAdd(a.off + list + 1, 1u)] =
@@ -672,8 +832,13 @@ __global__ void __launch_bounds__(256) zero_kernel(float4* p, int64_t n) {
 }
 
 size_t run_lds_bytes(const ResidentPlan& r) {
-    return (static_cast<size_t>(r.window) + 1) * r.n_local * sizeof(int) + static_cast<size_t>(r.threads / 64) * kListWords * sizeof(uint32_t);
+    const size_t lists = static_cast<size_t>(r.threads / 64) * kListWords * sizeof(uint32_t);
+    const size_t slots = (static_cast<size_t>(r.window) + 1) * (r.plastic ? r.words : r.n_local);
+    return ((slots + 1) & ~size_t(1)) * sizeof(int) + lists + (r.plastic ? static_cast<size_t>(r.n_local) * 12 : 0);
 }
+
+typedef void (*RunKernel)(RunArgs);
+RunKernel run_for(const ResidentPlan& r) { return r.plastic ? run_kernel<true> : run_kernel<false>; }
 
 }  // namespace
 
@@ -681,16 +846,17 @@ bool resident_fits(const ResidentPlan& r, int n_cu, size_t lds_max) {
     const size_t lds = run_lds_bytes(r);
     int per_cu = 0;
     return lds + 1024 <= lds_max && r.groups <= r.threads &&
-           hipFuncSetAttribute(reinterpret_cast<const void*>(&run_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+           hipFuncSetAttribute(reinterpret_cast<const void*>(run_for(r)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                static_cast<int>(lds_max - 1024)) == hipSuccess &&
-           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, run_kernel, r.threads, lds) == hipSuccess &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, run_for(r), r.threads, lds) == hipSuccess &&
            per_cu >= 1 && r.groups <= n_cu;
 }
 
 // (`sums`: one word per 4,096 entries of the offsets)
 hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, uint32_t* off, int64_t n_off, uint2* edge, uint32_t* sums,
                                   int lg, hipStream_t s) {
-    TableArgs a{g.src, g.w, g.d, g.rowstart, g.chunk_row0, off, edge, g.n_chunks, g.n_total, r.n_local, r.set_groups, r.window, lg};
+    TableArgs a{g.src, g.w, g.d, g.rowstart, g.chunk_row0, off, edge, r.plastic ? g.slot_orig : nullptr, g.row_first, r.info,
+                g.n_chunks, g.n_total, r.n_local, r.set_groups, r.window, lg, r.words};
     const dim3 chunks(static_cast<unsigned>((g.n_chunks + 3) / 4)), blocks(static_cast<unsigned>((n_off + kScanBlock - 1) / kScanBlock));
     table_kernel<false><<<chunks, dim3(256), 0, s>>>(a);
     scan_sums_kernel<<<blocks, dim3(256), 0, s>>>(off, n_off, sums);
@@ -739,6 +905,15 @@ hipError_t launch_resident(const DeviceGraph& g, const ResidentPlan& r, int64_t 
     a.rec_v = rec ? rec->v : nullptr;
     a.rec_input = rec ? rec->input : nullptr;
     a.caller_of = g.caller_of;
+    a.info = r.info;
+    a.wq = g.wq;
+    a.row_first = g.row_first;
+    a.spk_hist = g.spk_hist;
+    a.spk_cnt = g.spk_cnt;
+    a.dt = g.p0.dt_d;
+    a.alpha = g.stdp_alpha;
+    a.beta = g.stdp_beta;
+    a.words = r.words;
     a.t0 = t0;
     a.n_total = g.n_total;
     a.n_pad = g.n_pad;
@@ -759,7 +934,7 @@ hipError_t launch_resident(const DeviceGraph& g, const ResidentPlan& r, int64_t 
     a.inv_unit = r.inv_unit;
     a.params = g.params;
     void* args[] = {&a};
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&run_kernel), dim3(r.groups), dim3(r.threads), args,
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(run_for(r)), dim3(r.groups), dim3(r.threads), args,
                                       static_cast<unsigned>(run_lds_bytes(r)), s);
 }
 

@@ -83,3 +83,35 @@ def test_resident_timing_window_and_oracle():
         g[key] = torch.cat([p[name] for p in parts]).cpu().numpy().astype(np.float64)
     check_parity(g, oracle.OracleNet(spec).step(720, v=True, inp=True))
     net.close()
+
+
+def _learning(n, k, delays=None, burst=False):
+    """A plastic network with inhibitory weights and weights that start at zero."""
+    s = _burst(n, k) if burst else _lif(n, k, 0.05, delays)
+    s.weight = s.weight.copy()
+    s.weight[::5] *= -1.0
+    s.weight[::7] = 0.0
+    return synth.plastic(s, alpha=0.02, beta=0.1)
+
+
+@pytest.mark.parametrize("args", [(2, 0), (65, 1, [1, 254, 255]), (1000, 2, [1, 2, 30, 90]), (700, 3, None, True),
+                                  (20001, 4, [1, 2, 25])])
+def test_resident_plastic_equals_per_step(args):
+    """The same for weights that learn: every weight, and the spike times that
+    the next call starts from."""
+    import torch
+    import paper_0908_3934_amd as gn
+    spec = _learning(*args)
+    print(args, spec.src.size, flush=True)
+    nets = [gn.Net(spec), gn.Net(spec, flags=gn.NET_BUILD_REORDER), gn.Net(spec, flags=gn.NET_BUILD_PER_STEP)]
+    for c, T in enumerate(CALLS):
+        outs = [x.step(T, raster=True, v=True, inp=True) for x in nets]
+        w = [x.observe(gn.NET_OBS_WEIGHTS) for x in nets]
+        torch.cuda.synchronize()
+        for k in range(2):
+            for key in ("raster", "v", "input"):
+                assert torch.equal(outs[k][key], outs[2][key]), (c, k, key)
+            assert torch.equal(w[k], w[2]), (c, k)
+    assert spec.src.size < 10 or int((w[2].cpu() != torch.tensor(spec.weight)).sum()) > spec.src.size // 20
+    for x in nets:
+        x.close()
