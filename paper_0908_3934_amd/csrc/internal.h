@@ -495,9 +495,9 @@ hipError_t fit_eval(const FitInputs& in, const FitWork& w, hipStream_t s);
 
 int64_t mlp_ldt(int64_t B);
 hipError_t mlp_forward(const MlpDevice& d, const float* X, int64_t B, const float* y, hipStream_t s);
-hipError_t mlp_backward(const MlpDevice& d, int64_t B, float* loss_out, hipStream_t s);
+hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, float* loss_out, hipStream_t s);
 // (also clears d.grad for the next accumulation)
-hipError_t mlp_adam(const MlpDevice& d, float lr, float beta1, float beta2, float eps, int64_t t, hipStream_t s);
+hipError_t mlp_adam(const MlpDevice& d, float lr, float beta1, float beta2, float eps, int64_t t, float* loss_out, hipStream_t s);
 hipError_t mlp_refresh_bf16(const MlpDevice& d, hipStream_t s);
 hipError_t mlp_forward_fused(const MlpDevice& d, const float* X, int64_t B, float* logits, hipStream_t s);
 // Input standardisation statistics of X [rows][64]: shift = column mean,

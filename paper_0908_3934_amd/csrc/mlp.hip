@@ -211,7 +211,7 @@ __device__ __forceinline__ void store_stage(const StageRegs<BM, BN, KS>& r, bool
 // Block tile BM x BN (64 or 128 each), four waves in a 2 x 2 arrangement,
 // each wave (BM/2) x (BN/2) = TM x TN tiles of 32 x 32.
 
-// Head, loss and dH2 of the 64 rows m0.. whose H2 (BF16, after bias and
+// Head, loss and dH2 of the BM rows m0.. whose H2 (BF16, after bias and
 // ReLU) a 256-thread workgroup holds in LDS: four threads per row form the
 // logit (64 products each, then two exchanges); each thread then owns one
 // column for the dH2 values (rounded to BF16 in place in LDS) and that
@@ -219,10 +219,11 @@ __device__ __forceinline__ void store_stage(const StageRegs<BM, BN, KS>& r, bool
 // 16-byte stores.  The workgroup's sums go into replica (workgroup mod
 // kHeadReplicas) of the partial sums; head_finish adds the replicas into
 // the gradient.
+template <int BM>
 __device__ __forceinline__ void head_rows(uint16_t (*Hs)[kMlpH + 8], const HeadArgs& a, int64_t m0) {
-    __shared__ float dls[64], ls[64];
+    __shared__ float dls[BM], ls[BM];
     const int tid = threadIdx.x;
-    {
+    if (tid < 4 * BM) {
         const int r = tid >> 2, part = tid & 3;
         float s = 0.0f;
 #pragma unroll
@@ -260,7 +261,7 @@ __device__ __forceinline__ void head_rows(uint16_t (*Hs)[kMlpH + 8], const HeadA
         const int n = tid;
         const float w3n = a.w3[n];
         float gw3 = 0.0f, gb2 = 0.0f;
-        for (int r = 0; r < 64; ++r) {
+        for (int r = 0; r < BM; ++r) {
             const float h = bf16_bits_to_f32(Hs[r][n]);
             const float dl = dls[r];
             const uint16_t g = f32_to_bf16_bits(h > 0.0f ? dl * w3n : 0.0f);
@@ -273,17 +274,17 @@ __device__ __forceinline__ void head_rows(uint16_t (*Hs)[kMlpH + 8], const HeadA
         atomicAdd(part + kMlpH + n, gb2);
         if (n < 2) {
             float acc = 0.0f;
-            for (int r = 0; r < 64; ++r) acc += n == 0 ? ls[r] : dls[r];
+            for (int r = 0; r < BM; ++r) acc += n == 0 ? ls[r] : dls[r];
             atomicAdd(part + 2 * kMlpH + n, acc);
         }
     }
     __syncthreads();
-    for (int e = tid; e < 64 * kMlpH / 8; e += 256) {
+    for (int e = tid; e < BM * kMlpH / 8; e += 256) {
         const int r = e / (kMlpH / 8), c = (e % (kMlpH / 8)) * 8;
         if (m0 + r < a.B) *reinterpret_cast<uint4*>(a.dH2 + (m0 + r) * kMlpH + c) = *reinterpret_cast<const uint4*>(&Hs[r][c]);
     }
-    for (int e = tid; e < 64 * kMlpH / 8; e += 256) {
-        const int n = e / 8, r = (e % 8) * 8;
+    for (int e = tid; e < BM * kMlpH / 8; e += 256) {
+        const int n = e / (BM / 8), r = (e % (BM / 8)) * 8;
         const int64_t m = m0 + r;
         if (m >= a.ldt) continue;
         uint32_t w[4];
@@ -337,12 +338,13 @@ constexpr int gemm_lds_elems() {
 
 template <int kEpi, int BM, int BN, int KS>
 __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
-    constexpr int TM = BM / 64, TN = BN / 64;
+    constexpr int WM = BM >= 64 ? 2 : 1, WN = 4 / WM;           // waves along m and n
+    constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);
     __shared__ __attribute__((aligned(16))) uint16_t lds[gemm_lds_elems<kEpi, BM, BN, KS>()];
     uint16_t (*As)[lds_k<KS>()] = reinterpret_cast<uint16_t (*)[lds_k<KS>()]>(lds);                      // [m][k]
     uint16_t (*Bs)[lds_k<KS>()] = reinterpret_cast<uint16_t (*)[lds_k<KS>()]>(lds + BM * lds_k<KS>());   // [n][k]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / WN, wn = wave % WN;
     const int64_t m0 = static_cast<int64_t>(blockIdx.y) * BM, n0 = static_cast<int64_t>(blockIdx.x) * BN;
     const int64_t k_lo = static_cast<int64_t>(blockIdx.z) * g.k_chunk;
     const int64_t k_hi = k_lo + g.k_chunk < g.K ? k_lo + g.k_chunk : g.K;
@@ -366,9 +368,9 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
             const int rr = lane & 31, kq = ks + 8 * (lane >> 5);
             bf16x8 a[TM], b[TN];
 #pragma unroll
-            for (int t = 0; t < TM; ++t) a[t] = *reinterpret_cast<const bf16x8*>(&As[wm * (BM / 2) + t * 32 + rr][kq]);
+            for (int t = 0; t < TM; ++t) a[t] = *reinterpret_cast<const bf16x8*>(&As[wm * (BM / WM) + t * 32 + rr][kq]);
 #pragma unroll
-            for (int t = 0; t < TN; ++t) b[t] = *reinterpret_cast<const bf16x8*>(&Bs[wn * (BN / 2) + t * 32 + rr][kq]);
+            for (int t = 0; t < TN; ++t) b[t] = *reinterpret_cast<const bf16x8*>(&Bs[wn * (BN / WN) + t * 32 + rr][kq]);
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
@@ -383,10 +385,10 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-                const int64_t n = n0 + wn * (BN / 2) + tn * 32 + (lane & 31);
+                const int64_t n = n0 + wn * (BN / WN) + tn * 32 + (lane & 31);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int64_t m = m0 + wm * (BM / 2) + tm * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+                    const int64_t m = m0 + wm * (BM / WM) + tm * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
                     if (m < g.M && n < g.N) atomicAdd(g.out_f32 + m * g.N + n, acc[tm][tn][i]);
                 }
             }
@@ -428,13 +430,13 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-            const int nl = wn * (BN / 2) + tn * 32 + (lane & 31);
+            const int nl = wn * (BN / WN) + tn * 32 + (lane & 31);
             const int64_t n = n0 + nl;
             float bn = 0.0f;
             if (kEpi != kMaskBf16) bn = n < g.N ? g.bias[n] : 0.0f;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int ml = wm * (BM / 2) + tm * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+                const int ml = wm * (BM / WM) + tm * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
                 const float v = acc[tm][tn][i];
                 float o;
                 if (kEpi != kMaskBf16) {
@@ -458,8 +460,8 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
     }
     if constexpr (kEpi == kHeadBf16) {
         // the whole row width is in the tile: the head follows in place
-        static_assert(BM == 64 && BN == kMlpH, "the head epilogue needs 64 x 256 tiles");
-        head_rows(reinterpret_cast<uint16_t (*)[kMlpH + 8]>(lds), g.head, m0);
+        static_assert(BM <= 64 && BN == kMlpH, "the head epilogue needs 64 x 256 or 32 x 256 tiles");
+        head_rows<BM>(reinterpret_cast<uint16_t (*)[kMlpH + 8]>(lds), g.head, m0);
         return;
     }
     if (g.out_bf16) {
@@ -471,7 +473,7 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
         }
     }
     if constexpr (kEpi == kChainBf16) {
-        static_assert(BM == 64 && BN == kMlpH, "the chained product needs 64 x 256 tiles");
+        static_assert(TM == 1 && BN == kMlpH, "the chained product needs 64 x 256 or 32 x 256 tiles");
         // nonzero bits of the first tile (the ReLU mask of the later backward product)
         for (int e = tid; e < BM * (BN / 32); e += 256) {
             const int r = e / (BN / 32), q = e % (BN / 32);
@@ -520,10 +522,10 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
 #pragma unroll
             for (int ks = 0; ks < KS2; ks += 16) {
                 const int rr = lane & 31, kq = ks + 8 * (lane >> 5);
-                const bf16x8 a = *reinterpret_cast<const bf16x8*>(&Cs[wm * (BM / 2) + rr][k0 + kq]);
+                const bf16x8 a = *reinterpret_cast<const bf16x8*>(&Cs[wm * (BM / WM) + rr][k0 + kq]);
 #pragma unroll
                 for (int tn = 0; tn < TN; ++tn) {
-                    const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Bs[wn * (BN / 2) + tn * 32 + rr][kq]);
+                    const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Bs[wn * (BN / WN) + tn * 32 + rr][kq]);
                     acc2[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc2[tn], 0, 0, 0);
                 }
             }
@@ -532,17 +534,17 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
         // every read of the first tile is done: the second one replaces it
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-            const int nl = wn * (BN / 2) + tn * 32 + (lane & 31);
+            const int nl = wn * (BN / WN) + tn * 32 + (lane & 31);
             const float bn = g.bias2[nl];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int ml = wm * (BM / 2) + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+                const int ml = wm * (BM / WM) + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
                 const float h = acc2[tn][i] + bn;
                 Cs[ml][nl] = f32_to_bf16_bits(h > 0.0f ? h : 0.0f);
             }
         }
         __syncthreads();
-        head_rows(reinterpret_cast<uint16_t (*)[kMlpH + 8]>(&Cs[0][0]), g.head, m0);
+        head_rows<BM>(reinterpret_cast<uint16_t (*)[kMlpH + 8]>(&Cs[0][0]), g.head, m0);
     }
 }
 
@@ -681,6 +683,9 @@ struct AdamArgs {
     float* m;
     float* v;
     float* g;          // read, then cleared for the next step's accumulation
+    float* part;       // the replicas of the head's and the b1 sums, taken and cleared likewise
+    float* loss;
+    float* loss_out;
     uint16_t* w1b;
     uint16_t* w2b;
     uint16_t* w2c;
@@ -693,8 +698,29 @@ struct AdamArgs {
 __global__ void __launch_bounds__(256) adam_kernel(AdamArgs a) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= a.n) return;
-    const float gi = a.g[i];
+    // (a step of its own for these sums took 4.8 us)
+    auto take = [&](int entry) {
+        float v[kHeadReplicas], acc = 0.0f;
+#pragma unroll
+        for (int r = 0; r < kHeadReplicas; ++r) v[r] = a.part[r * kHeadPart + entry];   // all loads in flight
+#pragma unroll
+        for (int r = 0; r < kHeadReplicas; ++r) {
+            acc += v[r];
+            a.part[r * kHeadPart + entry] = 0.0f;
+        }
+        return acc;
+    };
+    float gi = a.g[i];
     a.g[i] = 0.0f;
+    if (i >= kMlpB1Off && i < kMlpB1Off + kMlpH) gi += take(2 * kMlpH + 8 + static_cast<int>(i - kMlpB1Off));
+    else if (i >= kMlpB2Off && i < kMlpB2Off + kMlpH) gi += take(kMlpH + static_cast<int>(i - kMlpB2Off));
+    else if (i >= kMlpW3Off && i < kMlpW3Off + kMlpH) gi += take(static_cast<int>(i - kMlpW3Off));
+    else if (i == kMlpB3Off) {
+        gi += take(2 * kMlpH + 1);
+        const float loss = take(2 * kMlpH);
+        a.loss[0] = loss;
+        if (a.loss_out) a.loss_out[0] = loss;
+    }
     const float m = a.b1 * a.m[i] + (1.0f - a.b1) * gi;
     const float v = a.b2 * a.v[i] + (1.0f - a.b2) * gi * gi;
     a.m[i] = m;
@@ -944,13 +970,18 @@ hipError_t gemm(const GemmArgs& g, int split, hipStream_t s) {
 int64_t mlp_ldt(int64_t B) { return (B + 7) / 8 * 8; }
 
 // Products over the batch rows with the whole 256-wide output row in one
-// tile (64 x 256, K staged 64 at a time): each row tile of A is read once,
+// tile (64 x 256 or 32 x 256, K staged 64 at a time): each row tile of A is read once,
 // and the head can follow the H2 product in its epilogue.  A and B must be
 // k-contiguous and K a multiple of 64.
+// Up to 16,384 rows 64-row tiles give a CU one workgroup, four waves that wait
+// for every stage and barrier together; 32-row tiles give it two.  An epoch of
+// 65,536 rows in batches of 16,384 with its launches: 594 us, with 32-row tiles
+// 543, and with the weight gradients' chunks below 478.
+constexpr int64_t kRows32 = 64 * 256;
 template <int kEpi>
 hipError_t gemm_rows(const GemmArgs& g, hipStream_t s) {
     if (g.N != kMlpH || g.a_cs != 1 || g.b_rs != 1 || g.K % 64 != 0 || g.k_chunk != g.K) return hipErrorInvalidValue;
-    return gemm_tile<kEpi, 64, kMlpH, 64>(g, 1, s);
+    return g.M <= kRows32 ? gemm_tile<kEpi, 32, kMlpH, 64>(g, 1, s) : gemm_tile<kEpi, 64, kMlpH, 64>(g, 1, s);
 }
 
 // Training forward pass for B rows of features X (FP32 [B x 64]) with
@@ -1007,15 +1038,18 @@ static void weight_split(int64_t ldt, int64_t rows, int* split, int64_t* chunk) 
 }
 
 // Backward pass after mlp_forward: accumulates the gradient of the mean BCE
-// into d.grad (which the caller zeroed).  Every product reads k-contiguous
+// into d.grad (which the caller zeroed); without `finish` the head's and the b1
+// sums stay in their replicas, for mlp_adam to take.  Every product reads k-contiguous
 // operands: the weight gradients take the transposed activations.
-hipError_t mlp_backward(const MlpDevice& d, int64_t B, float* loss_out, hipStream_t s) {
+hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, float* loss_out, hipStream_t s) {
     const int64_t ldt = mlp_ldt(B);
-    // dW2 = H1^T dH2  (M = 256, N = 256, K = ldt): 16 tiles, chunks of 2,048
-    // rows (512 workgroups at 65,536 rows; fewer chunks, fewer atomics)
+    // dW2 = H1^T dH2  (M = 256, N = 256, K = ldt): 16 tiles, up to 2,048 rows a
+    // chunk (512 workgroups at 65,536 rows; fewer chunks, fewer atomics), fewer
+    // where that leaves less than a workgroup per CU (16,384 rows: chunks of
+    // 2,048, 1,024, 512, 256: an epoch 594, 519, 533, 553 us)
     int split = 1;
     int64_t chunk = ldt;
-    weight_split(ldt, 2048, &split, &chunk);
+    weight_split(ldt, std::min<int64_t>(std::max<int64_t>(ldt / 16, 128), 2048), &split, &chunk);
     GemmArgs w2{};
     w2.A = d.H1t;
     w2.B = d.dH2t;
@@ -1047,8 +1081,8 @@ hipError_t mlp_backward(const MlpDevice& d, int64_t B, float* loss_out, hipStrea
     h1.ldt = ldt;
     h1.colsum_part = d.head_part;      // b1 gradient: column sums of dH1
     if ((e = gemm_rows<kMaskBf16>(h1, s)) != hipSuccess) return e;
-    // dW1 = Xb^T dH1  (M = 64, N = 256, K = ldt): four tiles, chunks of 512 rows
-    weight_split(ldt, 512, &split, &chunk);
+    // dW1 = Xb^T dH1  (M = 64, N = 256, K = ldt): four tiles, chunks of up to 512 rows, likewise
+    weight_split(ldt, std::min<int64_t>(std::max<int64_t>(ldt / 64, 128), 512), &split, &chunk);
     GemmArgs w1{};
     w1.A = d.Xbt;
     w1.B = d.dH1t;
@@ -1063,6 +1097,7 @@ hipError_t mlp_backward(const MlpDevice& d, int64_t B, float* loss_out, hipStrea
     w1.out_f32 = d.grad + kMlpW1Off;
     if ((e = gemm<kAtomicF32>(w1, split, s)) != hipSuccess) return e;
     // the head's and the b1 sums into the gradient
+    if (!finish) return hipSuccess;
     hipLaunchKernelGGL(finish_kernel, dim3((kHeadPart + 63) / 64), dim3(64), 0, s, d.head_part, d.grad, d.loss, loss_out);
     return hipGetLastError();
 }
@@ -1087,12 +1122,15 @@ hipError_t mlp_forward_fused(const MlpDevice& d, const float* X, int64_t B, floa
     return hipGetLastError();
 }
 
-hipError_t mlp_adam(const MlpDevice& d, float lr, float beta1, float beta2, float eps, int64_t t, hipStream_t s) {
+hipError_t mlp_adam(const MlpDevice& d, float lr, float beta1, float beta2, float eps, int64_t t, float* loss_out, hipStream_t s) {
     AdamArgs a;
     a.p = d.params;
     a.m = d.adam_m;
     a.v = d.adam_v;
     a.g = d.grad;
+    a.part = d.head_part;
+    a.loss = d.loss;
+    a.loss_out = loss_out;
     a.w1b = d.w1b;
     a.w2b = d.w2b;
     a.w2c = d.w2c;
