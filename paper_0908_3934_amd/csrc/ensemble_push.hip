@@ -32,6 +32,8 @@
 namespace geonet {
 namespace {
 
+constexpr int kPushOwnGroups = 4;
+
 struct PushArgs {
     const PushNet* __restrict__ nets;       // [blocks] in launch order
     const uint32_t* __restrict__ off;       // per network n x n_win + 1 edge offsets: entry s n_win + w opens
@@ -86,6 +88,7 @@ struct PushCtx {
     int noise_at;             // the network's first value in a row of the noise drawn ahead
     float unit, inv_unit;     // one unit of the slots' integers and its inverse (0: the slots hold floats)
     bool obs, last_net;
+    bool own;                 // every wave pushes its own vertices' spikes (see push_run)
 };
 
 // Adds the edges [e0, e1) of every lane into the input slots, the
@@ -171,6 +174,13 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
     const uint32_t words = c.n_win * static_cast<uint32_t>(c.groups);
     const uint32_t my_w = static_cast<uint32_t>(lane) * c.groups_inv >> 20;       // window and group of the lane's
     const uint32_t my_g = static_cast<uint32_t>(lane) - my_w * static_cast<uint32_t>(c.groups);   // first word
+    // Small LIF networks of one window: a wave's own spikes, which it has in
+    // registers, straight away; nothing is shared (256 vertices, 1,000 steps:
+    // 568 us shared, 407 so).  In larger ones the spikes of a step gather in few
+    // waves, and where a lane has several vertices the second form's code alone
+    // costs 4 %.
+    constexpr bool kOwn = kModel == NET_MODEL_LIF && VPT == 1;
+    const bool own = kOwn && c.own;
     uint64_t spk[VPT];                       // this wave's spikes of the step to come
 #pragma unroll
     for (int q = 0; q < VPT; ++q) spk[q] = c.hist[bucket * c.groups + (q < c.nq ? c.wave + q * c.waves : c.wave)];
@@ -253,7 +263,7 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
             }
             // the step's words of spike bits (window w's of step t - w W); the first 64 here
             uint64_t word = 0;
-            if (static_cast<uint32_t>(lane) < words) {
+            if (!own && static_cast<uint32_t>(lane) < words) {
                 int at = static_cast<int>(bucket) - static_cast<int>(my_w * W);
                 at = at < 0 ? at + static_cast<int>(c.buckets) : at;
                 word = c.hist[static_cast<uint32_t>(at * c.groups) + my_g];
@@ -337,7 +347,22 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
             // ---- push: every wave takes each `waves`-th of the spikes, 64 words at a
             // time (all of this in one branch: on a step without spikes nothing
             // waits for the memory accesses in flight)
-            for (uint32_t k0 = 0; k0 < words; k0 += 64u) {
+            if constexpr (kOwn) {
+                if (own) {
+#pragma unroll
+                    for (int q = 0; q < VPT; ++q) {
+                        if (q >= nq || spk[q] == 0) continue;
+                        uint32_t e0 = 0u, e1 = 0u;
+                        if ((spk[q] >> lane) & 1u) {
+                            const uint32_t o = static_cast<uint32_t>((c.wave + q * c.waves) * 64 + lane);
+                            e0 = c.off[o];
+                            e1 = c.off[o + 1u];
+                        }
+                        push_lists(c, e0, e1, slot);
+                    }
+                }
+            }
+            for (uint32_t k0 = own ? words : 0u; k0 < words; k0 += 64u) {
                 uint32_t word_w = my_w, word_g = my_g;
                 if (k0 != 0u) {
                     const uint32_t k = k0 + static_cast<uint32_t>(lane);
@@ -380,7 +405,7 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
                 bool spike = false;
                 if (q < nq) spike = push_spikes<kModel>(S, q, p);
                 spk[q] = wave_ballot(spike);
-                if (q < nq && lane == 0) c.hist[bucket * static_cast<uint32_t>(c.groups) + c.wave + q * c.waves] = spk[q];
+                if (!own && q < nq && lane == 0) c.hist[bucket * static_cast<uint32_t>(c.groups) + c.wave + q * c.waves] = spk[q];
             }
             slot = slot + 1u == c.slots ? 0u : slot + 1u;
             lds_barrier();
@@ -427,7 +452,7 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
 // step, for large ones VALU issue on one CU and the two dependent loads of a
 // spiking wave (offsets, edges).  Measured, us per step, before (two barriers,
 // delivery pulled or pushed by one wave) and now: one quiet LIF network of 256
-// vertices 2.46 / 0.56; 128 LIF networks of 64 .. 4096 8.9 / 1.8; 512 of them
+// vertices 2.46 / 0.41; 128 LIF networks of 64 .. 4096 8.9 / 1.8; 512 of them
 // 8.1 / 2.3; 40 Izhikevich networks (the largest 1,000 vertices, 2e5 edges)
 // 38 / 7.6; the same as Hodgkin-Huxley networks 49 / 6.1.
 template <int kModels, int VPT, int kThreads>
@@ -457,6 +482,7 @@ __global__ void __launch_bounds__(kThreads) push_ensemble_kernel(PushArgs args) 
     c.stride = static_cast<uint32_t>(c.groups) * 64u;
     c.obs = a->calcium != nullptr;
     c.last_net = nm.node_off + nm.n == a->n_total;
+    c.own = c.n_win == 1u && c.groups <= kPushOwnGroups;
     c.unit = nm.unit;
     c.inv_unit = nm.inv_unit;
     c.off = a->off + nm.off_at;
