@@ -115,3 +115,39 @@ def test_resident_plastic_equals_per_step(args):
     assert spec.src.size < 10 or int((w[2].cpu() != torch.tensor(spec.weight)).sum()) > spec.src.size // 20
     for x in nets:
         x.close()
+
+
+def test_resident_on_streams_of_two_threads():
+    """Two networks, a thread and a stream each: cooperative launches of one
+    process take turns on the device, and each gives what it gives alone."""
+    import threading
+    import torch
+    import paper_0908_3934_amd as gn
+    specs = [_lif(1000, 8, 0.05), _lif(20000, 9, 0.05)]
+    alone = []
+    for s in specs:
+        net = gn.Net(s)
+        alone.append([net.step(64, raster=True, v=True) for _ in range(4)])
+        torch.cuda.synchronize()
+        net.close()
+    nets, got = [gn.Net(s) for s in specs], [None, None]
+    torch.cuda.synchronize()
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            got[k] = [nets[k].step(64, raster=True, v=True) for _ in range(4)]
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+        assert not t.is_alive()
+    torch.cuda.synchronize()
+    for k in range(2):
+        for a, b in zip(alone[k], got[k]):
+            for key in ("raster", "v"):
+                assert torch.equal(a[key], b[key]), (k, key)
+        nets[k].close()
