@@ -495,7 +495,18 @@ hipError_t fit_eval(const FitInputs& in, const FitWork& w, hipStream_t s);
 
 int64_t mlp_ldt(int64_t B);
 hipError_t mlp_forward(const MlpDevice& d, const float* X, int64_t B, const float* y, hipStream_t s);
-hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, float* loss_out, hipStream_t s);
+// Rows [a0, a0 + count) of the permutation (seed, epoch) of [0, rows) into xs, ys.
+struct MlpGather {
+    const float* X;
+    const float* y;
+    int64_t rows;
+    uint64_t seed;
+    uint32_t epoch;
+    int64_t a0, count;
+    float* xs;
+    float* ys;
+};
+hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, const MlpGather* next, float* loss_out, hipStream_t s);
 // (also clears d.grad for the next accumulation)
 hipError_t mlp_adam(const MlpDevice& d, float lr, float beta1, float beta2, float eps, int64_t t, float* loss_out, hipStream_t s);
 hipError_t mlp_refresh_bf16(const MlpDevice& d, hipStream_t s);
@@ -507,8 +518,7 @@ constexpr int kStatBlocks = 512;
 hipError_t mlp_input_stats(const float* X, int64_t rows, double* work, float* shift, float* scale, hipStream_t s);
 // Rows [a0, a0 + count) of the order given by the keyed permutation of
 // [0, rows) for (seed, epoch), gathered into xs [count][64] and ys [count].
-hipError_t gather_shuffled(const float* X, const float* y, int64_t rows, uint64_t seed, uint32_t epoch, int64_t a0,
-                           int64_t count, float* xs, float* ys, hipStream_t s);
+hipError_t gather_shuffled(const MlpGather& g, hipStream_t s);
 // out[i] = permutation(i) for i < n.
 hipError_t shuffle_indices(int64_t n, uint64_t seed, uint32_t epoch, int64_t* out, hipStream_t s);
 

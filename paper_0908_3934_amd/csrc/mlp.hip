@@ -553,11 +553,87 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
     gemm_tile_of<kEpi, BM, BN, KS>(g, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
+// A keyed permutation of [0, n): a four-round balanced Feistel network on
+// 2h bits (2^(2h) >= n, so at most 4n values) whose round function is
+// Philox4x32-10 of (right half, round, epoch), walked until the value falls
+// below n (cycle walking; any permutation of the larger domain restricted
+// this way is a permutation of [0, n)).
+struct ShufflePerm {
+    uint64_t n;
+    uint32_t k0, k1, epoch;
+    int h;
+};
+
+__device__ __forceinline__ uint64_t shuffle_index(uint64_t i, const ShufflePerm& p) {
+    const uint32_t mask = (p.h >= 32) ? 0xFFFFFFFFu : ((1u << p.h) - 1u);
+    uint64_t x = i;
+    do {
+        uint32_t L = static_cast<uint32_t>(x >> p.h) & mask, R = static_cast<uint32_t>(x) & mask;
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint4 f = philox4x32_10(make_uint4(R, r, p.epoch, 0x53485546u), p.k0, p.k1);
+            const uint32_t nr = (L ^ f.x) & mask;
+            L = R;
+            R = nr;
+        }
+        x = (static_cast<uint64_t>(L) << p.h) | R;
+    } while (x >= p.n);
+    return x;
+}
+
+// Rows [a0, a0 + count) of the shuffled order gathered into xs / ys.
+struct GatherArgs {
+    const float* X;
+    const float* y;
+    ShufflePerm p;
+    int64_t a0, count;
+    float* xs;
+    float* ys;
+};
+
+__device__ __forceinline__ void gather_rows(const GatherArgs& g, int64_t i) {          // one thread per 16 floats
+    const int64_t r = i / 4;
+    if (r >= g.count) return;
+    const int part = static_cast<int>(i % 4);
+    const int64_t src = static_cast<int64_t>(shuffle_index(static_cast<uint64_t>(g.a0 + r), g.p));
+    const float4* in = reinterpret_cast<const float4*>(g.X + src * kMlpIn) + 4 * part;
+    float4* out = reinterpret_cast<float4*>(g.xs + r * kMlpIn) + 4 * part;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[k] = in[k];
+    if (part == 0) g.ys[r] = g.y[src];
+}
+
+ShufflePerm make_perm(int64_t n, uint64_t seed, uint32_t epoch) {
+    ShufflePerm p{};
+    p.n = static_cast<uint64_t>(n);
+    p.k0 = static_cast<uint32_t>(seed);
+    p.k1 = static_cast<uint32_t>(seed >> 32);
+    p.epoch = epoch;
+    int bits = 1;
+    while (bits < 63 && (uint64_t(1) << bits) < p.n) ++bits;
+    p.h = (bits + 1) / 2;
+    return p;
+}
+
+GatherArgs gather_args(const MlpGather& g) {
+    return GatherArgs{g.X, g.y, make_perm(g.rows, g.seed, g.epoch), g.a0, g.count, g.xs, g.ys};
+}
+
+__global__ void __launch_bounds__(256) gather_shuffled_kernel(GatherArgs g) {
+    gather_rows(g, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x);
+}
+
 // The two weight gradients in one launch (the first n2 workgroups dW2's tiles
-// and chunks, the others dW1's): neither fills the chip, and a launch is saved.
+// and chunks, up to n12 dW1's): neither fills the chip, and a launch is saved.
+// The workgroups from n12 on gather the next batch of an epoch, whose buffer
+// only the forward pass reads (5 us as a launch of its own).
 // 65,536 rows in batches of 16,384: an epoch 321 us apart, 298 together.
-__global__ void __launch_bounds__(256) weight_grads_kernel(GemmArgs w2, GemmArgs w1, int n2) {
+__global__ void __launch_bounds__(256) weight_grads_kernel(GemmArgs w2, GemmArgs w1, int n2, int n12, GatherArgs next) {
     const int t = static_cast<int>(blockIdx.x);
+    if (t >= n12) {
+        gather_rows(next, static_cast<int64_t>(t - n12) * 256 + threadIdx.x);
+        return;
+    }
     const bool second = t >= n2;
     const GemmArgs g = second ? w1 : w2;
     const int i = second ? t - n2 : t, nx = static_cast<int>(g.N / 64), ny = static_cast<int>(g.M / 64);
@@ -601,64 +677,9 @@ __global__ void __launch_bounds__(64) colstats_finish_kernel(const double* part,
     scale[c] = sd > 1e-6 ? static_cast<float>(1.0 / sd) : 0.0f;
 }
 
-// A keyed permutation of [0, n): a four-round balanced Feistel network on
-// 2h bits (2^(2h) >= n, so at most 4n values) whose round function is
-// Philox4x32-10 of (right half, round, epoch), walked until the value falls
-// below n (cycle walking; any permutation of the larger domain restricted
-// this way is a permutation of [0, n)).
-struct ShufflePerm {
-    uint64_t n;
-    uint32_t k0, k1, epoch;
-    int h;
-};
-
-__device__ __forceinline__ uint64_t shuffle_index(uint64_t i, const ShufflePerm& p) {
-    const uint32_t mask = (p.h >= 32) ? 0xFFFFFFFFu : ((1u << p.h) - 1u);
-    uint64_t x = i;
-    do {
-        uint32_t L = static_cast<uint32_t>(x >> p.h) & mask, R = static_cast<uint32_t>(x) & mask;
-#pragma unroll
-        for (uint32_t r = 0; r < 4; ++r) {
-            const uint4 f = philox4x32_10(make_uint4(R, r, p.epoch, 0x53485546u), p.k0, p.k1);
-            const uint32_t nr = (L ^ f.x) & mask;
-            L = R;
-            R = nr;
-        }
-        x = (static_cast<uint64_t>(L) << p.h) | R;
-    } while (x >= p.n);
-    return x;
-}
-
-// Rows [a0, a0 + count) of the shuffled order gathered into xs / ys.
-__global__ void __launch_bounds__(256) gather_shuffled_kernel(const float* X, const float* y, ShufflePerm p,
-                                                              int64_t a0, int64_t count, float* xs, float* ys) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;   // one thread per 16 floats
-    const int64_t r = i / 4;
-    if (r >= count) return;
-    const int part = static_cast<int>(i % 4);
-    const int64_t src = static_cast<int64_t>(shuffle_index(static_cast<uint64_t>(a0 + r), p));
-    const float4* in = reinterpret_cast<const float4*>(X + src * kMlpIn) + 4 * part;
-    float4* out = reinterpret_cast<float4*>(xs + r * kMlpIn) + 4 * part;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) out[k] = in[k];
-    if (part == 0) ys[r] = y[src];
-}
-
 __global__ void __launch_bounds__(256) shuffle_index_kernel(ShufflePerm p, int64_t* out) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < static_cast<int64_t>(p.n)) out[i] = static_cast<int64_t>(shuffle_index(static_cast<uint64_t>(i), p));
-}
-
-ShufflePerm make_perm(int64_t n, uint64_t seed, uint32_t epoch) {
-    ShufflePerm p{};
-    p.n = static_cast<uint64_t>(n);
-    p.k0 = static_cast<uint32_t>(seed);
-    p.k1 = static_cast<uint32_t>(seed >> 32);
-    p.epoch = epoch;
-    int bits = 1;
-    while (bits < 63 && (uint64_t(1) << bits) < p.n) ++bits;
-    p.h = (bits + 1) / 2;
-    return p;
 }
 
 // The head's replicas summed in a fixed order into the gradient (w3, b2, b3)
@@ -1055,9 +1076,10 @@ static void weight_split(int64_t ldt, int64_t rows, int* split, int64_t* chunk) 
 
 // Backward pass after mlp_forward: accumulates the gradient of the mean BCE
 // into d.grad (which the caller zeroed); without `finish` the head's and the b1
-// sums stay in their replicas, for mlp_adam to take.  Every product reads k-contiguous
+// sums stay in their replicas, for mlp_adam to take.  `next` (may be null): rows
+// gathered on the way, into what the forward pass of this batch has read.  Every product reads k-contiguous
 // operands: the weight gradients take the transposed activations.
-hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, float* loss_out, hipStream_t s) {
+hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, const MlpGather* next, float* loss_out, hipStream_t s) {
     const int64_t ldt = mlp_ldt(B);
     // dW2 = H1^T dH2  (M = 256, N = 256, K = ldt): 16 tiles, up to 2,048 rows a
     // chunk (512 workgroups at 65,536 rows; fewer chunks, fewer atomics), fewer
@@ -1114,11 +1136,14 @@ hipError_t mlp_backward(const MlpDevice& d, int64_t B, bool finish, float* loss_
     // together, unless their workgroups are so many that larger tiles pay (see gemm)
     const int64_t n2 = static_cast<int64_t>(kMlpH / 64 * (kMlpH / 64)) * split2, n1 = static_cast<int64_t>(kMlpH / 64) * split;
     if (n2 <= 8192 && n1 <= 8192) {
-        hipLaunchKernelGGL(weight_grads_kernel, dim3(static_cast<unsigned>(n2 + n1)), dim3(256), 0, s, w2, w1, static_cast<int>(n2));
+        const int64_t ng = next ? (next->count * 4 + 255) / 256 : 0;
+        hipLaunchKernelGGL(weight_grads_kernel, dim3(static_cast<unsigned>(n2 + n1 + ng)), dim3(256), 0, s, w2, w1, static_cast<int>(n2),
+                           static_cast<int>(n2 + n1), next ? gather_args(*next) : GatherArgs{});
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         if ((e = gemm<kAtomicF32>(w2, split2, s)) != hipSuccess) return e;
         if ((e = gemm<kAtomicF32>(w1, split, s)) != hipSuccess) return e;
+        if (next && (e = gather_shuffled(*next, s)) != hipSuccess) return e;
     }
     // the head's and the b1 sums into the gradient
     if (!finish) return hipSuccess;
@@ -1184,12 +1209,8 @@ hipError_t mlp_input_stats(const float* X, int64_t rows, double* work, float* sh
     return hipGetLastError();
 }
 
-hipError_t gather_shuffled(const float* X, const float* y, int64_t rows, uint64_t seed, uint32_t epoch, int64_t a0,
-                           int64_t count, float* xs, float* ys, hipStream_t s) {
-    const ShufflePerm p = make_perm(rows, seed, epoch);
-    const int64_t threads = count * 4;
-    hipLaunchKernelGGL(gather_shuffled_kernel, dim3(static_cast<unsigned>((threads + 255) / 256)), dim3(256), 0, s, X,
-                       y, p, a0, count, xs, ys);
+hipError_t gather_shuffled(const MlpGather& g, hipStream_t s) {
+    hipLaunchKernelGGL(gather_shuffled_kernel, dim3(static_cast<unsigned>((g.count * 4 + 255) / 256)), dim3(256), 0, s, gather_args(g));
     return hipGetLastError();
 }
 

@@ -181,8 +181,8 @@ net_status net_mlp_forward(net_mlp_t* m, const float* x_dev, int64_t rows, float
     return NET_OK;
 }
 
-static net_status grad_impl(net_mlp* m, const float* x, const float* y, int64_t rows, bool finish, float* loss_out,
-                            hipStream_t s) {
+static net_status grad_impl(net_mlp* m, const float* x, const float* y, int64_t rows, bool finish, const MlpGather* next,
+                            float* loss_out, hipStream_t s) {
     net_status st = check(m, rows, x);
     if (st != NET_OK) return st;
     if (!y) return mfail(NET_E_ARG, "net_mlp: labels are NULL");
@@ -191,7 +191,7 @@ static net_status grad_impl(net_mlp* m, const float* x, const float* y, int64_t 
     if (!m->grad_clear) e = hipMemsetAsync(m->d.grad, 0, kMlpParams * sizeof(float), s);
     m->grad_clear = false;
     if (e == hipSuccess) e = mlp_forward(m->d, x, rows, y, s);
-    if (e == hipSuccess) e = mlp_backward(m->d, rows, finish, loss_out, s);
+    if (e == hipSuccess) e = mlp_backward(m->d, rows, finish, next, loss_out, s);
     if (e != hipSuccess) return mdev(m, e, "net_mlp: gradient");
     return NET_OK;
 }
@@ -199,7 +199,7 @@ static net_status grad_impl(net_mlp* m, const float* x, const float* y, int64_t 
 net_status net_mlp_grad(net_mlp_t* m, const float* x_dev, const float* y_dev, int64_t rows, float* grad_dev,
                         float* loss_dev, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    net_status st = grad_impl(m, x_dev, y_dev, rows, true, loss_dev, s);
+    net_status st = grad_impl(m, x_dev, y_dev, rows, true, nullptr, loss_dev, s);
     if (st != NET_OK) return st;
     hipError_t e = hipSuccess;
     if (grad_dev) e = hipMemcpyAsync(grad_dev, m->d.grad, kMlpParams * sizeof(float), hipMemcpyDeviceToDevice, s);
@@ -207,17 +207,21 @@ net_status net_mlp_grad(net_mlp_t* m, const float* x_dev, const float* y_dev, in
     return NET_OK;
 }
 
-net_status net_mlp_train_step(net_mlp_t* m, const float* x_dev, const float* y_dev, int64_t rows, float lr,
-                              float* loss_dev, void* stream) {
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!(lr > 0.0f)) return mfail(NET_E_ARG, "net_mlp_train_step: lr must be > 0");
-    net_status st = grad_impl(m, x_dev, y_dev, rows, false, nullptr, s);
+static net_status train_impl(net_mlp* m, const float* x, const float* y, int64_t rows, float lr, const MlpGather* next,
+                             float* loss_out, hipStream_t s) {
+    net_status st = grad_impl(m, x, y, rows, false, next, nullptr, s);
     if (st != NET_OK) return st;
     m->adam_t += 1;
-    hipError_t e = mlp_adam(m->d, lr, 0.9f, 0.999f, 1e-8f, m->adam_t, loss_dev, s);
+    hipError_t e = mlp_adam(m->d, lr, 0.9f, 0.999f, 1e-8f, m->adam_t, loss_out, s);
     if (e != hipSuccess) return mdev(m, e, "net_mlp_train_step");
     m->grad_clear = true;
     return NET_OK;
+}
+
+net_status net_mlp_train_step(net_mlp_t* m, const float* x_dev, const float* y_dev, int64_t rows, float lr,
+                              float* loss_dev, void* stream) {
+    if (!(lr > 0.0f)) return mfail(NET_E_ARG, "net_mlp_train_step: lr must be > 0");
+    return train_impl(m, x_dev, y_dev, rows, lr, nullptr, loss_dev, static_cast<hipStream_t>(stream));
 }
 
 net_status net_mlp_fit_input_norm(net_mlp_t* m, const float* x_dev, int64_t rows, void* stream) {
@@ -266,12 +270,17 @@ net_status net_mlp_train_epoch(net_mlp_t* m, const float* x_dev, const float* y_
             return mfail(NET_E_OOM, "net_mlp_train_epoch: workspace");
         m->xs_cap = b;
     }
+    // the first batch is gathered by itself, every other one beside the weight
+    // gradients of the one before
+    MlpGather g{x_dev, y_dev, rows, shuffle_seed, epoch, 0, b, m->xs, m->ys};
+    hipError_t e = gather_shuffled(g, s);
+    if (e != hipSuccess) return mdev(m, e, "net_mlp_train_epoch: gather");
     int64_t k = 0;
     for (int64_t a0 = 0; a0 < rows; a0 += b, ++k) {
         const int64_t count = std::min(b, rows - a0);
-        hipError_t e = gather_shuffled(x_dev, y_dev, rows, shuffle_seed, epoch, a0, count, m->xs, m->ys, s);
-        if (e != hipSuccess) return mdev(m, e, "net_mlp_train_epoch: gather");
-        net_status st = net_mlp_train_step(m, m->xs, m->ys, count, lr, loss_dev ? loss_dev + k : nullptr, stream);
+        g.a0 = a0 + b;
+        g.count = std::min(b, rows - g.a0);
+        net_status st = train_impl(m, m->xs, m->ys, count, lr, g.a0 < rows ? &g : nullptr, loss_dev ? loss_dev + k : nullptr, s);
         if (st != NET_OK) return st;
     }
     return NET_OK;
