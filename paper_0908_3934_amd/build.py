@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgeonet.so")
 SOURCES = ["kernels.hip", "ensemble_push.hip", "resident.hip", "build.cpp", "abi.cpp", "mlp.hip", "mlp_abi.cpp", "estimate.hip", "estimate_abi.cpp", "simfit.hip",
            "features_noalloc.hip"]
-HEADERS = ["internal.h", "philox.h", "vertex.h", os.path.join("..", "..", "include", "geonet.h")]
+HEADERS = ["internal.h", "philox.h", "push_plan.h", "vertex.h", os.path.join("..", "..", "include", "geonet.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("GEONET_ARCH", "gfx950")

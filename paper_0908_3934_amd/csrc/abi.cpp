@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "push_plan.h"
 
 using namespace geonet;
 
@@ -319,22 +320,12 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
         pn.node_off = static_cast<int32_t>(hg.node_off[m]);
         pn.n = static_cast<int32_t>(n);
         pn.groups = static_cast<int32_t>((n + 63) / 64);
-        pn.tbits = 1;
-        while ((int64_t(1) << pn.tbits) < n) ++pn.tbits;
-        // The widest window that LDS and the edge word have room for: each
-        // further window of the delays is one more visit per spike.
-        size_t need = 0;
-        int W = std::min(hg.net_max_delay[m], 1 << (16 - pn.tbits));
-        for (; W >= 1; --W) {
-            const int nw = (hg.net_max_delay[m] + W - 1) / W;
-            const size_t ring = static_cast<size_t>(W + 1) * pn.groups * 64 * sizeof(float);
-            pn.hist_off = static_cast<int32_t>(ring);
-            pn.window = W;
-            pn.n_win = nw;
-            need = ring + (static_cast<size_t>(nw - 1) * W + 2) * pn.groups * 8 + 2 * 33 * sizeof(double);
-            if (need <= room) break;
-        }
-        if (W < 1) return false;
+        const PushShape shape = push_shape(n, hg.net_max_delay[m], room);
+        if (shape.window < 1) return false;
+        pn.tbits = shape.tbits;
+        pn.window = shape.window;
+        pn.n_win = shape.n_win;
+        pn.hist_off = static_cast<int32_t>(shape.ring);
         pn.off_at = off_len;
         pn.ring_at = ring_len;
         pn.hist_at = hist_len;
@@ -342,7 +333,7 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
         ring_len += static_cast<int64_t>(pn.window + 1) * pn.groups * 64;
         hist_len += (static_cast<int64_t>(pn.n_win - 1) * pn.window + 2) * pn.groups;
         *groups_max = std::max(*groups_max, pn.groups);
-        *lds_need = std::max(*lds_need, need);
+        *lds_need = std::max(*lds_need, shape.lds);
         cost[m] = (hg.net_chunk_end[m] - hg.net_chunk_begin[m]) * kChunkEdges + 8 * n;
     }
     // out-edges of every source by window (zero weights, the empty rows'

@@ -27,12 +27,15 @@
 
 #include "internal.h"
 #include "philox.h"
+#include "push_plan.h"
 #include "vertex.h"
 
 namespace geonet {
 namespace {
 
 constexpr int kPushOwnGroups = 4;
+static_assert(kPushThreads / 64 * kPushMaxVpt <= kWordMaxGroups && kPushThreadsFp64 / 64 * kPushMaxVptFp64 <= kWordMaxGroups,
+              "word_window is exact up to so many groups");
 
 struct PushArgs {
     const PushNet* __restrict__ nets;       // [blocks] in launch order
@@ -83,7 +86,7 @@ struct PushCtx {
     const double* pw;         // calcium over m steps without a spike: c -> c pw[m],
     const double* gs;         // its sum c gs[m]
     uint32_t stride, slots, n_win, tbits, buckets;
-    uint32_t groups_inv;      // ceil(2^20 / groups)
+    uint32_t groups_inv;      // word_inverse(groups)
     int n, groups, wave, waves, nq, node_off, lane;
     int noise_at;             // the network's first value in a row of the noise drawn ahead
     float unit, inv_unit;     // one unit of the slots' integers and its inverse (0: the slots hold floats)
@@ -172,7 +175,7 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
     uint32_t bucket = static_cast<uint32_t>(static_cast<uint64_t>(t0) % c.buckets);
     const uint32_t W = c.slots - 1u;
     const uint32_t words = c.n_win * static_cast<uint32_t>(c.groups);
-    const uint32_t my_w = static_cast<uint32_t>(lane) * c.groups_inv >> 20;       // window and group of the lane's
+    const uint32_t my_w = word_window(static_cast<uint32_t>(lane), c.groups_inv);   // window and group of the lane's
     const uint32_t my_g = static_cast<uint32_t>(lane) - my_w * static_cast<uint32_t>(c.groups);   // first word
     // Small LIF networks of one window: a wave's own spikes, which it has in
     // registers, straight away; nothing is shared (256 vertices, 1,000 steps:
@@ -366,7 +369,7 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
                 uint32_t word_w = my_w, word_g = my_g;
                 if (k0 != 0u) {
                     const uint32_t k = k0 + static_cast<uint32_t>(lane);
-                    word_w = k * c.groups_inv >> 20;
+                    word_w = word_window(k, c.groups_inv);
                     word_g = k - word_w * static_cast<uint32_t>(c.groups);
                     word = 0;
                     if (k < words) {
@@ -478,7 +481,7 @@ __global__ void __launch_bounds__(kThreads) push_ensemble_kernel(PushArgs args) 
     c.n_win = static_cast<uint32_t>(nm.n_win);
     c.tbits = static_cast<uint32_t>(nm.tbits);
     c.buckets = (c.n_win - 1u) * static_cast<uint32_t>(nm.window) + 2u;
-    c.groups_inv = ((1u << 20) + static_cast<uint32_t>(c.groups) - 1u) / static_cast<uint32_t>(c.groups);
+    c.groups_inv = word_inverse(static_cast<uint32_t>(c.groups));
     c.stride = static_cast<uint32_t>(c.groups) * 64u;
     c.obs = a->calcium != nullptr;
     c.last_net = nm.node_off + nm.n == a->n_total;
