@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
         }
         if (obs && t0_64 + k + 1 == next_flush) {
             const const_args r = reread(ka);
-            ++frame;
+            frame = next_flush * r->frame_num / r->frame_den;           // (frames shorter than a step: several further)
             frame_first = next_flush;
             next_flush = ((frame + 1) * r->frame_den + r->frame_num - 1) / r->frame_num;
         }
