@@ -680,18 +680,18 @@ net_status step_loop(net* h, int64_t n_steps, const net_record* rec, hipStream_t
 // calls below kResidentMinSteps stay with those, and where the ring of
 // arrivals has to be rebuilt first (about 100 us), calls below
 // kResidentMinRebuild.  A timing window times the step's kernels; a stream that
-// is being captured records them, and since its replays move the state unseen,
-// the handle then keeps to them.
+// is being captured records them, whatever the call's length, and since its
+// replays move the state unseen, the handle then keeps to them.
 bool resident_route(net* h, int64_t n_steps, hipStream_t s) {
     ResidentPlan& r = h->resident;
-    if (!r.enabled || n_steps < (r.valid ? kResidentMinSteps : kResidentMinRebuild) || h->t_cap != 0) return false;
+    if (!r.enabled) return false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         r.enabled = false;
         return false;
     }
-    return true;
+    return n_steps >= (r.valid ? kResidentMinSteps : kResidentMinRebuild) && h->t_cap == 0;
 }
 
 // A resident call ended at a wait's limit: the state it left is no step's.
