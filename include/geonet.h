@@ -355,6 +355,28 @@ net_status net_timing_end(net_t* h, net_timing_t* out);
 /* Sizes and counters of a handle (host struct). */
 net_status net_info(const net_t* h, net_info_t* out);
 
+/*
+ * How a handle uses the kernel that keeps its network resident on the chip
+ * (see NET_BUILD_PER_STEP).  Its workgroups exchange spikes, so all of them
+ * have to be on the chip: where another stream's kernels keep some of them off
+ * it for more than a second, one workgroup does the steps of that launch (at
+ * most 4,096) by itself, slowly and with the same results.  Should a workgroup
+ * that runs not hear from another one for seconds (which takes a fault of the
+ * machine), the launch ends: rows of its records from there on are NaN and, in
+ * the raster, all ones, whatever net_observe writes afterwards is NaN (-1 for
+ * NET_OBS_REF), and once the stream has come to that point `failed` is set and
+ * net_step_n and net_observe return NET_E_DEVICE.  A call does not wait for its
+ * stream, so the call itself and those right after it return NET_OK.
+ */
+typedef struct {
+    int32_t workgroups;     /* 0: the handle runs other kernels */
+    int32_t vertices;       /* per workgroup */
+    int32_t window;         /* steps of arrivals kept in LDS; longer delays wait in memory */
+    int32_t failed;
+    int64_t launches;       /* so far */
+} net_resident_t;
+net_status net_resident_info(const net_t* h, net_resident_t* out);
+
 /* First vertex index of every network: host int64 [n_nets + 1]. */
 net_status net_node_offsets(const net_t* h, int64_t* out);
 
@@ -516,6 +538,15 @@ const char* net_estimate_last_error(void);
  * handle except net_info, net_node_offsets and net_free returns NET_E_STATE.
  */
 net_status net_simulate_device_error(net_t* h);
+
+/*
+ * Error-handling test hook of the resident kernel: its next launches go as if
+ * their workgroups did not all get onto the chip (one of them does the steps),
+ * or as if the waits of their first step reached the limit (the launch gives
+ * up).  Every kernel ends normally.
+ */
+enum { NET_LOST_NEVER = 0, NET_LOST_AT_START = 1, NET_LOST_IN_STEP = 2 };
+net_status net_simulate_lost_workgroups(net_t* h, int32_t how);
 
 /* Release the handle and its device memory (waits for the handle's stream). */
 void net_free(net_t* h);

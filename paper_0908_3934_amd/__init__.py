@@ -181,6 +181,12 @@ class Net:
         _check(library().net_info(self.h, C.byref(out)), "net_info")
         return {name: getattr(out, name) for name, _ in _abi.Info._fields_}
 
+    def resident(self) -> dict:
+        """How the handle uses the kernel that keeps its network on the chip."""
+        out = _abi.Resident()
+        _check(library().net_resident_info(self.h, C.byref(out)), "net_resident_info")
+        return {name: getattr(out, name) for name, _ in _abi.Resident._fields_}
+
     def node_offsets(self) -> np.ndarray:
         out = np.zeros(len(self.specs) + 1, dtype=np.int64)
         _check(library().net_node_offsets(self.h, out.ctypes.data), "net_node_offsets")

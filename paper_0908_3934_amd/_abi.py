@@ -86,6 +86,14 @@ class Info(C.Structure):
     ]
 
 
+class Resident(C.Structure):
+    _fields_ = [("workgroups", C.c_int32), ("vertices", C.c_int32), ("window", C.c_int32), ("failed", C.c_int32),
+                ("launches", C.c_int64)]
+
+
+NET_LOST_NEVER, NET_LOST_AT_START, NET_LOST_IN_STEP = 0, 1, 2
+
+
 class Timing(C.Structure):
     _fields_ = [("deliver_ms", C.c_double), ("update_ms", C.c_double), ("ensemble_ms", C.c_double),
                 ("deliver_launches", C.c_int64), ("update_launches", C.c_int64),
@@ -127,6 +135,7 @@ SIGNATURES = {
     "net_step_n": (C.c_int, [_vp, C.c_int64, C.POINTER(Record), _vp]),
     "net_observe": (C.c_int, [_vp, C.c_int32, _vp, _vp, C.c_int64, _vp]),
     "net_info": (C.c_int, [_vp, C.POINTER(Info)]),
+    "net_resident_info": (C.c_int, [_vp, C.POINTER(Resident)]),
     "net_node_offsets": (C.c_int, [_vp, _vp]),
     "net_timing_begin": (C.c_int, [_vp, C.c_int64, C.c_int32]),
     "net_timing_end": (C.c_int, [_vp, C.POINTER(Timing)]),
@@ -149,6 +158,7 @@ SIGNATURES = {
     "net_shuffle_indices": (C.c_int, [C.c_int64, C.c_uint64, C.c_uint32, _vp, _vp]),
     "net_mlp_free": (None, [_vp]),
     "net_simulate_device_error": (C.c_int, [_vp]),
+    "net_simulate_lost_workgroups": (C.c_int, [_vp, C.c_int32]),
     "net_features_noalloc": (C.c_int, [_vp, _vp, _vp]),
     "net_features_noalloc_scratch_bytes": (C.c_size_t, [C.c_int32, C.c_int32]),
     "net_mlp_last_error": (C.c_char_p, []),

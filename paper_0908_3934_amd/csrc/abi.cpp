@@ -52,6 +52,10 @@ struct net {
 
 namespace {
 constexpr int64_t kResidentMinSteps = 8, kResidentMinRebuild = 128;
+// Steps of one resident launch: a launch costs about 20 us, these steps 7 ms or
+// more, and where a launch's workgroups do not come together, one workgroup does
+// no more than these.
+constexpr int64_t kResidentMaxSteps = 4096;
 constexpr int32_t kGraphSteps = 256;   // one replay: a whole turn of the history ring, an even number of steps
 }
 
@@ -486,6 +490,7 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     if (st == NET_OK) st = zeros(h, &sums, n_off / 4096 + 1, s, "resident edges");
     if (st == NET_OK) st = zeros(h, &r.head, resident_head_words(r), s, "spike exchange");
     if (st == NET_OK) st = zeros(h, &r.more, resident_more_words(r), s, "spike exchange");
+    if (st == NET_OK) st = zeros(h, &r.gate, resident_gate_words(r), s, "spike exchange");
     if (st == NET_OK && r.plastic) st = zeros(h, &r.info, static_cast<size_t>(hg.e_slots), s, "resident edges");
     if (st == NET_OK && ring_words != 0) {
         r.ring_mask = ring_slots - 1;
@@ -514,6 +519,7 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     r.valid = true;                                     // (no arrivals yet)
     r.enabled = true;
     h->resident = r;
+    g.lost = resident_lost(r);
     return NET_OK;
 }
 
@@ -709,7 +715,7 @@ net_status step_resident(net* h, int64_t n_steps, const net_record* rec, hipStre
         r.valid = true;
     }
     for (int64_t done = 0; done < n_steps;) {
-        const int32_t chunk = static_cast<int32_t>(std::min<int64_t>(n_steps - done, int64_t(1) << 29));
+        const int32_t chunk = static_cast<int32_t>(std::min<int64_t>(n_steps - done, kResidentMaxSteps));
         net_record sub{};
         if (rec) {
             const int64_t words = (h->g.n_total + 63) / 64;
@@ -727,6 +733,7 @@ net_status step_resident(net* h, int64_t n_steps, const net_record* rec, hipStre
         if (e == hipSuccess) e = launch_resident(h->g, r, h->t + done, chunk, rec ? &sub : nullptr, h->frame_num, h->frame_den, s);
         if (e != hipSuccess) return device_fail(h, e, "net_step_n: resident launch");
         r.seq += static_cast<uint32_t>(chunk);
+        ++r.launches;
         done += chunk;
     }
     advance_frames(h, h->t, n_steps);
@@ -1611,6 +1618,27 @@ net_status net_node_offsets(const net_t* h, int64_t* out) {
 net_status net_simulate_device_error(net_t* h) {
     if (!h) return fail(NET_E_ARG, "net_simulate_device_error: handle is NULL");
     h->broken = true;
+    return NET_OK;
+}
+
+net_status net_simulate_lost_workgroups(net_t* h, int32_t how) {
+    if (!h) return fail(NET_E_ARG, "net_simulate_lost_workgroups: handle is NULL");
+    if (how != NET_LOST_NEVER && how != NET_LOST_AT_START && how != NET_LOST_IN_STEP)
+        return fail(NET_E_ARG, "net_simulate_lost_workgroups: unknown kind");
+    h->resident.simulate = how;
+    return NET_OK;
+}
+
+net_status net_resident_info(const net_t* h, net_resident_t* out) {
+    if (!h || !out) return fail(NET_E_ARG, "net_resident_info: NULL argument");
+    std::memset(out, 0, sizeof(*out));
+    const ResidentPlan& r = h->resident;
+    out->launches = static_cast<int64_t>(r.launches);
+    out->failed = r.fail && __atomic_load_n(r.fail, __ATOMIC_RELAXED) != 0u ? 1 : 0;
+    if (!r.enabled) return NET_OK;
+    out->workgroups = r.groups;
+    out->vertices = r.n_local;
+    out->window = r.window;
     return NET_OK;
 }
 

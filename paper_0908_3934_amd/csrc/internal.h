@@ -254,6 +254,7 @@ struct DeviceGraph {
     int32_t* spk_hist = nullptr;
     int32_t* spk_cnt = nullptr;
     double stdp_alpha = 0.0, stdp_beta = 0.0;
+    const uint64_t* lost = nullptr;       // resident kernel (null otherwise): not 0 once its state is no step's
     // graph replays: the device step counter (null outside a captured
     // graph's launches) and the frame rule for the in-kernel bookkeeping
     const uint64_t* t_dev = nullptr;
@@ -335,6 +336,9 @@ struct ResidentPlan {
     float* ring = nullptr;          // device [ring_mask + 1][n_pad]
     uint64_t* head = nullptr;
     uint64_t* more = nullptr;
+    uint64_t* gate = nullptr;       // device: the workgroups' start (resident.hip)
+    uint64_t launches = 0;
+    int32_t simulate = 0;           // NET_LOST_*
     uint32_t* fail = nullptr;       // host memory and its device address
     uint32_t* fail_dev = nullptr;
     float unit = 0.0f, inv_unit = 0.0f;
@@ -342,6 +346,9 @@ struct ResidentPlan {
 bool resident_fits(const ResidentPlan& r, int n_cu, size_t lds_max);
 size_t resident_head_words(const ResidentPlan& r);
 size_t resident_more_words(const ResidentPlan& r);
+size_t resident_gate_words(const ResidentPlan& r);
+// Device word that is not 0 once a launch gave up.
+const uint64_t* resident_lost(const ResidentPlan& r);
 // Out-edge tables of the resident kernel from the handle's edges (off: zero; lg: the weights' unit is 2^lg).
 hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, uint32_t* off, int64_t n_off, uint2* edge, uint32_t* sums,
                                   int lg, hipStream_t s);

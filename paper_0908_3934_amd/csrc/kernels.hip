@@ -1278,6 +1278,7 @@ struct ObserveArgs {
     const NetParams* __restrict__ params;
     const int32_t* __restrict__ net_id;
     const int32_t* __restrict__ internal_of;   // renumbered networks: internal index of each caller's vertex
+    const uint64_t* __restrict__ lost;         // (null: none) not 0: the state is no step's, NaN or -1 goes out
     void* out;
     int64_t n_total, n_pad, n_frames;
     int32_t what, multi;
@@ -1292,6 +1293,11 @@ __global__ void __launch_bounds__(256) observe_kernel(ObserveArgs a) {
     const int64_t f = idx / a.n_total, jc = idx - f * a.n_total;
     const int64_t j = a.internal_of ? a.internal_of[jc] : jc;
     const NetParams& p = a.params[a.multi ? a.net_id[j] : 0];
+    if (a.lost && *a.lost != 0) {
+        if (a.what == NET_OBS_REF) static_cast<int32_t*>(a.out)[idx] = -1;
+        else static_cast<float*>(a.out)[idx] = __builtin_nanf("");
+        return;
+    }
     switch (a.what) {
         case NET_OBS_V:
             static_cast<float*>(a.out)[jc] = a.V[j];
@@ -1844,11 +1850,11 @@ __global__ void __launch_bounds__(256) plastic_deliver_kernel(PlasticArgs a) {
 }
 
 __global__ void __launch_bounds__(256) weights_out_kernel(const int32_t* wq, const int32_t* slot_orig, int64_t slots,
-                                                          float* out) {
+                                                          const uint64_t* lost, float* out) {
     const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (s >= slots) return;
     const int32_t o = slot_orig[s];
-    if (o >= 0) out[o] = static_cast<float>(static_cast<double>(wq[s]) * (1.0 / 1048576.0));
+    if (o >= 0) out[o] = lost && *lost != 0 ? __builtin_nanf("") : static_cast<float>(static_cast<double>(wq[s]) * (1.0 / 1048576.0));
 }
 
 }  // namespace
@@ -1934,7 +1940,7 @@ hipError_t launch_plastic_deliver(const DeviceGraph& g, int64_t t, hipStream_t s
 
 hipError_t launch_weights_out(const DeviceGraph& g, float* out, hipStream_t s) {
     hipLaunchKernelGGL(weights_out_kernel, dim3(static_cast<unsigned>((g.e_slots + 255) / 256)), dim3(256), 0, s, g.wq,
-                       g.slot_orig, g.e_slots, out);
+                       g.slot_orig, g.e_slots, g.lost, out);
     return hipGetLastError();
 }
 
@@ -1948,6 +1954,7 @@ hipError_t launch_observe(const DeviceGraph& g, int32_t what, const net_fluor_pa
     a.params = g.params;
     a.net_id = g.net_id;
     a.internal_of = g.internal_of;
+    a.lost = g.lost;
     a.out = out;
     a.n_total = g.n_total;
     a.n_pad = g.n_pad;

@@ -11,9 +11,21 @@
 // and the others as the number says.  A word is one 8-byte access, so it needs
 // no order towards any other.  Four sets of words in turn are enough: a
 // workgroup publishes t + 2 after it has read all words of t, whose owners had
-// read all words of t - 2 before they published them.  The launch is
-// cooperative (all workgroups are on the chip together), and every wait has a
-// limit, after which the launch ends and the handle fails.
+// read all words of t - 2 before they published them.
+//
+// Start.  The launch is cooperative, which gives every workgroup its place on an
+// idle chip, but one that another stream's kernels fill takes them in as those
+// end.  So each marks a word of its own when it starts, and nothing of the state
+// changes before it has seen every other's mark.  One that has waited for a
+// second closes the first word that is still unmarked: if that succeeds, its
+// owner cannot mark it any more and nobody sees all marks, so it does all the
+// steps by itself (run_alone), and whoever meets the closed word leaves.  All
+// words before a closed one are marked, so there is at most one.  (A call of 128
+// steps, 256 workgroups: 2.4 us for these words; one count that all add to takes
+// 5.4.)  From then on all run, and waits end within microseconds; should one
+// reach its limit all the same (polls for seconds), the launch ends, what it
+// leaves is marked (V and the rest of the records NaN or all ones, and every
+// later read-out NaN) and the handle fails.
 //
 // Delivery.  Out-edges are kept by (set of workgroups, source, workgroup of the
 // target), so a workgroup finds its part of a spike's edges with one load of
@@ -49,6 +61,12 @@ constexpr uint32_t kHeadMany = 15u;               // its count where they do not
 constexpr uint32_t kFar = kResidentFar;
 constexpr uint32_t kNoEdge = 0xFFFFFFFFu;
 constexpr uint32_t kSpinLimit = 1u << 22;         // polls (a few seconds)
+constexpr uint64_t kStartTicks = 100000000u;      // of the 100 MHz clock
+// Words of `gate`, 128 bytes apart: every workgroup's start (2 x the launch's
+// number, or that and 1: closed), one that nobody marks, and whether a launch
+// gave up.
+constexpr int kGateStep = 16;
+enum { kRun = 0, kLeave = 1, kLate = 2, kAlone = 4, kLost = 8 };      // bits: what a workgroup's waves saw
 
 struct RunArgs {
     const uint32_t* __restrict__ off;   // [sets][n_total][set_groups] and one more: first edge
@@ -57,6 +75,7 @@ struct RunArgs {
     float* ring;                        // [ring_mask + 1][n_pad] arrivals by step
     uint64_t* head;                     // [kSets][groups] first words, kHeadStep apart
     uint64_t* more;                     // [kSets][groups] second words, then [kSets][groups][n_local / 32] words of spike bits
+    uint64_t* gate;
     uint32_t* fail;                     // host memory: set where a wait reached its limit
     float* __restrict__ V;
     uint16_t* __restrict__ age;
@@ -82,6 +101,8 @@ struct RunArgs {
     int32_t* spk_cnt;
     double dt, alpha, beta;
     int64_t t0, n_total, n_pad, raster_words;
+    uint64_t launch;                    // 2 x the launch's number
+    uint32_t simulate;                  // NET_LOST_*
     uint32_t ring_mask, seq0;
     int32_t words;                      // of a step's arrivals, a bit per slot of the group
     int32_t n_steps, n_local, set_groups, window, max_delay, d_sum, sum_shift, frame_cap, frame_num, frame_den;
@@ -217,6 +238,190 @@ __device__ __forceinline__ void deliver_spikes(const RunCtx& c, bool have, uint3
     }
 }
 
+// Weight e of an edge (`info`) whose spike arrived at step `now`, or whose
+// target, with its last spike before at step tl (-1: none), fired there.
+__device__ __forceinline__ void learn(const RunArgs __attribute__((address_space(4)))& r, int64_t e, uint32_t info, int32_t tl, int64_t now) {
+    const int32_t w = r.wq[e];
+    const double since = now <= 0 ? 0.0 : (tl < 0 ? static_cast<double>(now) * r.dt : static_cast<double>(now - tl - 1) * r.dt);
+    const double q = since_spike(r.spk_hist, info & 0xFFFFu, now - ((info >> 16) & 0xFFu), r.dt) - since;
+    const double sg = q > 0.0 ? 1.0 : (q < 0.0 ? -1.0 : 0.0);
+    const double dw = r.dt * r.alpha * sg * exp(-r.beta * fabs(q));
+    r.wq[e] = w + static_cast<int32_t>(rint(dw * 1048576.0));
+}
+
+// One thread, after a second: closes the first word without a mark, unless
+// all words have one by now or one is closed.
+__device__ uint32_t close_start(uint64_t* gate, uint64_t launch, int words) {
+    for (int g = 0; g < words;) {
+        uint64_t now = __hip_atomic_load(gate + g * kGateStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (now > launch) return kLeave;
+        if (now == launch) ++g;
+        else if (__hip_atomic_compare_exchange_strong(gate + g * kGateStep, &now, launch + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT))
+            return kAlone;
+    }
+    return kRun;
+}
+
+// Marks this workgroup's start and waits for the others': what the workgroup
+// has to do (`role`: a word in LDS).
+__device__ __forceinline__ uint32_t start_role(const const_args a, uint32_t* role) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = static_cast<int>(blockDim.x >> 6);
+    const int groups = static_cast<int>(gridDim.x);
+    uint64_t* const gate = a->gate;
+    const uint64_t launch = a->launch;
+    const bool simulate = a->simulate == NET_LOST_AT_START;
+    if (tid == 0) {
+        const uint64_t was = __hip_atomic_fetch_max(gate + blockIdx.x * kGateStep, launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t lost = __hip_atomic_load(gate + (groups + 1) * kGateStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *role = (was > launch ? kLeave : kRun) | (lost != 0 ? kLost : kRun);
+    }
+    lds_barrier();
+    const int g = lane * waves + wave;
+    const uint64_t since = wall_clock64();
+    uint32_t saw = simulate ? kLate : kRun;
+    while (saw == kRun) {
+        const uint64_t v = g < groups ? __hip_atomic_load(gate + g * kGateStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : launch;
+        if (wave_ballot(v > launch) != 0) saw = kLeave;
+        else if (wave_ballot(v < launch) == 0) break;
+        else if (wall_clock64() - since >= kStartTicks) saw = kLate;
+    }
+    if (lane == 0 && saw != kRun) atomicOr(role, saw);
+    lds_barrier();
+    uint32_t r = *role;
+    lds_barrier();
+    if (!(r & kLeave) && (r & kLate)) {
+        if (tid == 0) *role = close_start(gate, launch, groups + (simulate ? 1 : 0)) | (r & kLost);
+        lds_barrier();
+        r = *role;
+    }
+    return __builtin_amdgcn_readfirstlane(r);
+}
+
+// The launch's steps by one workgroup, for a launch whose workgroups did not
+// come together: from and to the same state in memory, with the same sums.
+// Vertex j is thread j mod blockDim's in every step.  us per step: 8,192 vertices
+// 28, 262,144 960; 16,384 with weights that learn 2,600.
+template <bool kPlastic>
+__device__ __attribute__((noinline)) void run_alone(const const_args a) {
+    const uint32_t groups = gridDim.x;
+    const NetParams p = load_const(a->params);
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
+    const int64_t n_total = a->n_total, n_pad = a->n_pad;
+    const uint32_t sg = static_cast<uint32_t>(a->set_groups), n_local = static_cast<uint32_t>(a->n_local);
+    const int32_t n_steps = a->n_steps;
+    for (int32_t k = 0; k < n_steps; ++k) {
+        const int64_t t64 = a->t0 + k;
+        const uint32_t t = static_cast<uint32_t>(t64);
+        const int64_t frame = t64 * a->frame_num / a->frame_den;
+        const int64_t first = (frame * a->frame_den + a->frame_num - 1) / a->frame_num;
+        const bool flush = a->calcium && ((frame + 1) * a->frame_den + a->frame_num - 1) / a->frame_num == t64 + 1;
+        for (int64_t j = tid; j - lane < n_total; j += threads) {
+            const bool valid = j < n_total;
+            bool spike = false;
+            if (valid) {
+                const uint32_t ages = a->age[j], a1 = ages & 0xFFu, a2 = ages >> 8;
+                const float V = a->V[j];
+                spike = V >= p.v_th;
+                // the step's input
+                float in;
+                uint32_t* const hist = a->hist ? a->hist + j : nullptr;
+                [[maybe_unused]] auto arrives = [&](uint32_t info) {
+                    const uint32_t ts = t - ((info >> 16) & 0xFFu);
+                    return ((a->hist[static_cast<int64_t>((ts & 0xFFu) >> 5) * n_pad + (info & 0xFFFFu)] >> (ts & 31u)) & 1u) != 0u;
+                };
+                if constexpr (kPlastic) {
+                    long long sum = 0;
+                    for (int64_t e = a->row_first[j]; e < a->row_first[j + 1]; ++e) {
+                        const uint32_t info = a->info[e];
+                        if (info != kNoEdge && arrives(info)) sum += a->wq[e];
+                    }
+                    in = static_cast<float>(static_cast<double>(sum) * (1.0 / 1048576.0));
+                } else {
+                    // (the adds of earlier steps are in the L2)
+                    in = __hip_atomic_exchange(a->ring + static_cast<int64_t>(t & a->ring_mask) * n_pad + j, 0.0f, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (a->rec_v) a->rec_v[static_cast<int64_t>(k) * n_total + j] = V;
+                if (a->rec_input) a->rec_input[static_cast<int64_t>(k) * n_total + j] = in;
+                const uint32_t thr = a->drive_thr ? a->drive_thr[j] : 0u;
+                float u = a->i_ext ? a->i_ext[j] : 0.0f, noise = 0.0f;
+                if (thr != 0u || p.sigma != 0.0f) {
+                    const uint4 r = philox4x32_10(make_uint4(static_cast<uint32_t>(a->caller_of ? a->caller_of[j] : j), t,
+                                                             static_cast<uint32_t>(static_cast<uint64_t>(t64) >> 32), 0u),
+                                                  p.key_lo, p.key_hi);
+                    u = r.x < thr ? u + p.drive_amp : u;
+                    if (p.sigma != 0.0f) noise = p.sigma * gaussian(r.y, r.z);
+                }
+                const float vn = V + p.decay * (p.v_rest - V) + in + u + noise;
+                const bool held = a1 - 1u < static_cast<uint32_t>(p.n_ref);
+                a->V[j] = (spike | held) ? p.v_reset : vn;
+                const uint32_t o1 = a1 < 255u ? a1 + 1u : 255u, o2 = a2 < 255u ? a2 + 1u : 255u;
+                a->age[j] = static_cast<uint16_t>(spike ? 1u | o1 << 8 : o1 | o2 << 8);
+                if (a->calcium) {
+                    const double cal = a->calcium[j];
+                    double acc = a->frame_acc[j] + cal;
+                    if (flush) {
+                        if (frame < a->frame_cap) a->frames[frame * n_pad + j] = static_cast<float>(acc / static_cast<double>(t64 + 1 - first));
+                        acc = 0.0;
+                    }
+                    a->frame_acc[j] = acc;
+                    a->calcium[j] = cal + p.dt_d * (-cal / p.tau_c_d + (spike ? 1.0 : 0.0));
+                }
+                if (hist) {
+                    uint32_t& word = hist[static_cast<int64_t>((t & 0xFFu) >> 5) * n_pad];
+                    word = (word & ~(1u << (t & 31u))) | ((spike ? 1u : 0u) << (t & 31u));
+                }
+                if constexpr (kPlastic) {
+                    const int32_t count = a->spk_cnt[j];
+                    const int32_t tl = count > 0 ? __hip_atomic_load(a->spk_hist + j * kStdpHist + (count - 1) % kStdpHist, __ATOMIC_RELAXED,
+                                                                      __HIP_MEMORY_SCOPE_AGENT)
+                                                 : -1;
+                    if (spike) {
+                        __hip_atomic_store(a->spk_hist + j * kStdpHist + count % kStdpHist, static_cast<int32_t>(t), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        a->spk_cnt[j] = count + 1;
+                    }
+                    for (int64_t e = a->row_first[j]; e < a->row_first[j + 1]; ++e) {
+                        const uint32_t info = a->info[e];
+                        if (info != kNoEdge && (spike || arrives(info))) learn(*a, e, info, tl, t64);
+                    }
+                }
+            }
+            const uint64_t spk = wave_ballot(spike);
+            if (a->rec_raster && lane == 0) a->rec_raster[static_cast<int64_t>(k) * a->raster_words + (j >> 6)] = spk;
+            if constexpr (!kPlastic) {
+                for (uint64_t m = spk; m != 0; m &= m - 1) {
+                    const int64_t src = j - lane + __builtin_ctzll(m);
+                    for (uint32_t g = lane; g < groups; g += 64u) {
+                        const int64_t list = (static_cast<int64_t>(g / sg) * n_total + src) * sg + g % sg;
+                        for (uint32_t e = a->off[list]; e < a->off[list + 1]; ++e) {
+                            const uint2 x = a->edge[e];
+                            const uint32_t d = (x.x & kFar) ? (x.x >> 16) & 0xFFu : x.x / n_local;
+                            const uint32_t to = g * n_local + ((x.x & kFar) ? x.x & 0xFFFFu : x.x % n_local);
+                            __hip_atomic_fetch_add(a->ring + static_cast<int64_t>((t + d) & a->ring_mask) * n_pad + to,
+                                                   static_cast<float>(static_cast<int>(x.y)) * a->unit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                    }
+                }
+            }
+        }
+        // what the threads left for each other is there before the next step
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_barrier();
+    }
+    for (int64_t j = tid; a->summary && j - lane < n_pad; j += threads) {
+        const uint64_t recent = wave_ballot(j < n_total && (a->age[j] & 0xFFu) <= static_cast<uint32_t>(a->d_sum));
+        if (lane == 0) put_summary(a->summary, j, recent, a->sum_shift);
+    }
+    // the words' tags as if they had been published: none is taken for a later step's
+    const uint32_t end = a->seq0 + static_cast<uint32_t>(n_steps);
+    for (uint32_t i = tid; i < kSets * groups; i += threads) {
+        const uint32_t set = i / groups, next = end + (set + kSets - end % kSets) % kSets;
+        a->head[static_cast<int64_t>(i) * kHeadStep] = (next - kSets) & 0xFFFFu;
+    }
+}
+
 // What bounds it: the chain of a step, that is the look at the words, the two
 // dependent loads of the spikes' edges, the LDS adds, two barriers and the
 // update; at 1,024 vertices a CU also the noise (Philox and Box-Muller, 0.3 us a
@@ -239,9 +444,16 @@ template <bool kPlastic>
 __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     extern __shared__ uint4 lds4[];
     __shared__ uint64_t s_words[2][16];
-    __shared__ uint32_t s_dead;
+    __shared__ uint32_t s_dead, s_role;
     (void)args;
     const const_args ka = (const_args)__builtin_amdgcn_kernarg_segment_ptr();
+    // ---- nothing is written before all workgroups have started
+    const uint32_t role = start_role(reread(ka), &s_role);
+    if (role & kLeave) return;
+    if (role & kAlone) {
+        run_alone<kPlastic>(reread(ka));
+        return;
+    }
     const_args a = reread(ka);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = static_cast<int>(blockDim.x >> 6);
@@ -277,10 +489,11 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
     const uint32_t many_words = static_cast<uint32_t>(n_local) >> 5;
     const int64_t t0_64 = a->t0;
     const uint32_t t0 = static_cast<uint32_t>(t0_64), seq0 = a->seq0;
+
     const int32_t n_steps = a->n_steps;
 
     // ---- state in: the arrivals of steps t0 .. t0 + W - 1 move to LDS
-    if (tid == 0) s_dead = 0u;
+    if (tid == 0) s_dead = role & kLost || a->simulate == NET_LOST_IN_STEP ? 1u : 0u;
     const uint32_t slot0 = static_cast<uint32_t>(static_cast<uint64_t>(t0_64) % (W + 1u));
     const uint32_t quads = static_cast<uint32_t>(n_local) >> 2;         // (four vertices at a time, four such loads in flight)
     for (uint32_t i0 = tid; !kPlastic && i0 < (W + 1u) * quads; i0 += 4u * blockDim.x) {
@@ -513,20 +726,11 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
         if constexpr (kPlastic) {
             const const_args r = reread(ka);
             const int64_t now = t0_64 + k;
-            auto learn = [&](int64_t e, uint32_t info) {
-                const uint32_t to = info >> 24;
-                const int32_t tl = tlast[to], w = r->wq[e];
-                const double since = now <= 0 ? 0.0 : (tl < 0 ? static_cast<double>(now) * r->dt : static_cast<double>(now - tl - 1) * r->dt);
-                const double q = since_spike(r->spk_hist, info & 0xFFFFu, now - ((info >> 16) & 0xFFu), r->dt) - since;
-                const double sg = q > 0.0 ? 1.0 : (q < 0.0 ? -1.0 : 0.0);
-                const double dw = r->dt * r->alpha * sg * exp(-r->beta * fabs(q));
-                r->wq[e] = w + static_cast<int32_t>(rint(dw * 1048576.0));
-            };
             const uint64_t* const fired = s_words[seq & 1u];
             for (uint32_t m = arrived; m != 0u; m &= m - 1u) {
                 const int64_t e = first_slot + tid * 32 + __builtin_ctz(m);
                 const uint32_t info = r->info[e], to = info >> 24;
-                if (!((fired[to >> 6] >> (to & 63u)) & 1u)) learn(e, info);       // (else with all of its target's below)
+                if (!((fired[to >> 6] >> (to & 63u)) & 1u)) learn(*r, e, info, tlast[to], now);       // (else with all of its target's below)
             }
             int turn = 0;
             for (int x = 0; x < own_words; ++x) {
@@ -535,7 +739,7 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
                     const int64_t to = j0 + x * 64 + __builtin_ctzll(m), e1 = r->row_first[to + 1];
                     for (int64_t e = r->row_first[to] + lane; e < e1; e += 64) {
                         const uint32_t info = r->info[e];
-                        if (info != kNoEdge) learn(e, info);
+                        if (info != kNoEdge) learn(*r, e, info, tlast[info >> 24], now);
                     }
                 }
             }
@@ -642,7 +846,10 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
         ++row;
         slot = slot == W ? 0u : slot + 1u;
         if (s_dead != 0u) {
-            if (tid == 0) __hip_atomic_store(reread(ka)->fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (tid == 0) {
+                __hip_atomic_store(reread(ka)->gate + (groups + 1) * kGateStep, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(reread(ka)->fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
             break;
         }
     }
@@ -650,6 +857,17 @@ __global__ void __launch_bounds__(1024) run_kernel(RunArgs args) {
 
     // ---- state out
     a = reread(ka);
+    if (s_dead != 0u) {
+        // no step's state: V and the records that are left say so
+        const uint64_t all = wave_ballot(valid);
+        const int64_t from = s_role & kLost ? 0 : row;
+        for (int64_t q = from; valid && q < a->n_steps; ++q) {
+            if (raster) raster[(q - row) * raster_words] = all;
+            if (a->rec_v) a->rec_v[q * n_total + j] = __builtin_nanf("");
+            if (a->rec_input) a->rec_input[q * n_total + j] = __builtin_nanf("");
+        }
+        V = __builtin_nanf("");
+    }
     const uint32_t t1 = t0 + static_cast<uint32_t>(row);
     for (uint32_t i = tid; !kPlastic && i < W * quads; i += blockDim.x) {
         const uint32_t k = i / quads, v = (i - k * quads) * 4u, s = slot + k > W ? slot + k - (W + 1u) : slot + k;
@@ -867,6 +1085,8 @@ hipError_t launch_resident_tables(const DeviceGraph& g, const ResidentPlan& r, u
 }
 
 size_t resident_head_words(const ResidentPlan& r) { return static_cast<size_t>(kSets) * r.groups * kHeadStep; }
+size_t resident_gate_words(const ResidentPlan& r) { return (static_cast<size_t>(r.groups) + 2) * kGateStep; }
+const uint64_t* resident_lost(const ResidentPlan& r) { return r.gate + (static_cast<size_t>(r.groups) + 1) * kGateStep; }
 size_t resident_more_words(const ResidentPlan& r) { return static_cast<size_t>(kSets) * r.groups * (1 + r.n_local / 32); }
 
 hipError_t launch_resident_renumber(const ResidentPlan& r, hipStream_t s) {
@@ -891,6 +1111,7 @@ hipError_t launch_resident(const DeviceGraph& g, const ResidentPlan& r, int64_t 
     a.ring = r.ring;
     a.head = r.head;
     a.more = r.more;
+    a.gate = r.gate;
     a.fail = r.fail_dev;
     a.V = g.V;
     a.age = g.age;
@@ -918,6 +1139,8 @@ hipError_t launch_resident(const DeviceGraph& g, const ResidentPlan& r, int64_t 
     a.n_total = g.n_total;
     a.n_pad = g.n_pad;
     a.raster_words = (g.n_total + 63) / 64;
+    a.launch = 2 * (r.launches + 1);
+    a.simulate = static_cast<uint32_t>(r.simulate);
     a.ring_mask = r.ring_mask;
     a.seq0 = r.seq;
     a.n_steps = n_steps;
