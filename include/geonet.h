@@ -156,8 +156,11 @@ enum { NET_PSC_NONE = 0, NET_PSC_EXP = 1, NET_PSC_ALPHA = 2 };
 /* Build options; a zeroed struct (or NULL) selects the defaults. */
 typedef struct {
     int32_t frame_capacity;       /* frames kept per vertex; 0 disables calcium */
-    int32_t block_threads;        /* delivery workgroup size override (0 = auto) */
-    int32_t blocks_per_cu;        /* delivery workgroups per CU override (0 = auto) */
+    int32_t block_threads;        /* workgroup size override of delivery and of the single-launch
+                                     kernels (0 = auto) */
+    int32_t blocks_per_cu;        /* workgroups per CU override of delivery and of the single-launch
+                                     kernel that has several networks per workgroup, which is then
+                                     used (0 = auto) */
     int32_t flags;                /* NET_BUILD_* */
 } net_build_opts;
 
@@ -237,8 +240,9 @@ typedef struct {
 #define NET_BUILD_AUTOTUNE 64             /* time the candidate launch shapes on this graph at
                                              build (a few steps from the initial state, which is
                                              then restored) and keep the fastest: delivery
-                                             variants for the per-step kernels, workgroup size and
-                                             workgroups per CU for the single-launch kernel.
+                                             variants for the per-step kernels, the workgroup size
+                                             for the single-launch push kernel, workgroup size and
+                                             workgroups per CU for the one that larger networks take.
                                              Every candidate computes the same bits. */
 
 /*

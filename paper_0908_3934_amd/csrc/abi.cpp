@@ -1169,11 +1169,12 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
         int sb = 1;
         while ((int64_t(1) << sb) < max_n) ++sb;
         g.ens_sbits = sb >= 16 || int64_t(hg.max_delay) >= (int64_t(1) << (16 - sb)) ? 16 : sb;
-        // the push ensemble kernel where every network fits its registers and LDS
+        // the push ensemble kernel where every network fits its registers and
+        // LDS, unless the caller sets the workgroups per CU, of which it has none to set
         const int models = hg.any_hh ? 2 : (hg.any_izh ? 1 : 0);
         int dev = 0, n_cu = 0, lds_max = 0, groups_max = 1;
         size_t lds_need = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
+        if (!(opts && opts->blocks_per_cu) && hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
             hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
             plan_push(h, hg, models, n_cu, static_cast<size_t>(lds_max), s, &groups_max, &lds_need, &st)) {
