@@ -287,12 +287,12 @@ bool load_plan(net* h, const HostGraph& hg, int n_cu, int per_cu, int threads, b
 // Push ensemble kernel: its launch shape for at most `threads` threads per
 // workgroup.  Returns false where some network has more vertices than the
 // workgroup's registers hold.
-bool shape_push(net* h, int models, int threads, int groups_max, size_t lds_bytes) {
+bool shape_push(net* h, int models, int threads, int groups_max) {
     const int cap = models > 0 ? kPushThreadsFp64 : kPushThreads;
     const int waves = std::max(1, std::min(std::min(threads, cap) / 64, groups_max));
     int vpt = 1;
     while (vpt * waves < groups_max) vpt *= 2;
-    if (vpt > (models > 0 ? kPushMaxVptFp64 : kPushMaxVpt) || enable_push_ensemble(models, vpt, lds_bytes) != hipSuccess) return false;
+    if (vpt > (models > 0 ? kPushMaxVptFp64 : kPushMaxVpt) || enable_push_ensemble(models, vpt) != hipSuccess) return false;
     h->plan.threads = waves * 64;
     h->plan.vpt = vpt;
     return true;
@@ -325,7 +325,7 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
                net_status* st) {
     const int n_nets = h->g.n_nets;
     const int cap = models > 0 ? kPushThreadsFp64 * kPushMaxVptFp64 : kPushThreads * kPushMaxVpt;
-    const size_t room = std::min<size_t>(lds_max, 152 * 1024);
+    const size_t room = std::min<size_t>(lds_max, kPushMaxLds);
     std::vector<PushNet> nets(n_nets);
     std::vector<int64_t> cost(n_nets);
     int64_t off_len = 0, ring_len = 0, hist_len = 0;
@@ -1198,7 +1198,7 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
             int best = -1;
             double best_ms = 0.0;
             for (size_t k = 0; k < shapes.size(); ++k) {
-                if (!shape_push(h, models, shapes[k], groups_max, lds_need)) continue;
+                if (!shape_push(h, models, shapes[k], groups_max)) continue;
                 if (shapes.size() == 1) {
                     best = 0;
                     break;
@@ -1219,7 +1219,7 @@ net_status net_build(const net_desc* descs, int32_t n_nets, const net_build_opts
             }
             // (an explicit shape too small for the largest network: the widest one)
             if (best < 0) shapes.assign(1, most);
-            pl.enabled = shape_push(h, models, shapes[best < 0 ? 0 : best], groups_max, lds_need);
+            pl.enabled = shape_push(h, models, shapes[best < 0 ? 0 : best], groups_max);
             if (!pl.enabled) {
                 device_fail(h, hipErrorUnknown, "net_build: ensemble plan");
                 return bail(NET_E_DEVICE);

@@ -659,9 +659,10 @@ PushKernel push_kernel(int models, int vpt) {
 
 }  // namespace
 
-hipError_t enable_push_ensemble(int models, int vpt, size_t lds_bytes) {
+// (the same for every handle: the attribute is the kernel's)
+hipError_t enable_push_ensemble(int models, int vpt) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(push_kernel(models, vpt)),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
+                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kPushMaxLds));
 }
 
 hipError_t launch_push_ensemble(const DeviceGraph& g, const EnsemblePlan& plan, int64_t t0, int32_t n_steps,

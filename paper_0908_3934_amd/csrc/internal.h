@@ -111,6 +111,7 @@ struct PushNet {
 // registers per thread hold eight, with FP64 models 256 registers hold four.
 constexpr int kPushThreads = 1024, kPushMaxVpt = 8;
 constexpr int kPushThreadsFp64 = 512, kPushMaxVptFp64 = 4;
+constexpr size_t kPushMaxLds = 152 * 1024;      // bytes of LDS a network may take
 
 // Host-side result of graph construction (before upload).
 struct HostGraph {
@@ -400,7 +401,7 @@ hipError_t launch_ensemble(const DeviceGraph& g, const EnsemblePlan& plan, int64
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // Push ensemble kernel (ensemble_push.hip); models: 0 LIF only, 1 with
 // Izhikevich networks, 2 with Hodgkin-Huxley networks.
-hipError_t enable_push_ensemble(int models, int vpt, size_t lds_bytes);
+hipError_t enable_push_ensemble(int models, int vpt);
 hipError_t launch_push_ensemble(const DeviceGraph& g, const EnsemblePlan& plan, int64_t t0, int32_t n_steps,
                                 const net_record* rec, int32_t frame_num, int32_t frame_den, hipStream_t s,
                                 hipEvent_t ev0, hipEvent_t ev1);

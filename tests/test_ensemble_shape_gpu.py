@@ -26,3 +26,20 @@ def test_workgroups_per_cu(per_cu, threads):
             assert torch.equal(x[key], z[key]) and torch.equal(y[key], z[key]), key
     for net in (a, b, c):
         net.close()
+
+
+def test_lds_of_two_handles():
+    """A handle that needs little LDS, built after one that needs most of it and
+    stepped before it."""
+    import torch
+    import paper_0908_3934_amd as gn
+    big, small = [_lif(900, 1, 0.0, [1, 100, 255]), _lif(64, 2, 0.05)], [_lif(900, 3, 0.0, [1]), _lif(64, 4, 0.05)]
+    ref = [gn.Net(s, flags=gn.NET_BUILD_PER_STEP) for s in (small, big)]
+    b, a = gn.Net(big), gn.Net(small)
+    for T in (40, 200):
+        for net, per_step in zip((a, b), ref):
+            x, y = net.step(T, raster=True, v=True), per_step.step(T, raster=True, v=True)
+            torch.cuda.synchronize()
+            assert torch.equal(x["raster"], y["raster"]) and torch.equal(x["v"], y["v"])
+    for net in [a, b] + ref:
+        net.close()
