@@ -247,12 +247,12 @@ def bench_ensemble(args, torch, synth, gn):
     net.close()
     log("ensemble: %d steps in %.3f s (kernel %.3f ms)" % (steps, wall, tm["ensemble_ms"]))
     # sequential: every k-th network alone with its best setting (the
-    # single-launch LDS-resident kernel, autotuned; the two per-step kernels
-    # over the whole GPU; the fused per-step kernel), scaled to all
+    # single-launch kernel on one CU, autotuned; the kernel that spreads a
+    # network over the chip; the two per-step kernels), scaled to all
     sample = specs[::args.seq_sample]
     seq = 0.0
-    variants = [("single-launch", gn.NET_BUILD_SINGLE_LAUNCH | gn.NET_BUILD_AUTOTUNE), ("per-step", 0),
-                ("fused step", gn.NET_BUILD_FUSED_STEP)]
+    variants = [("single-launch", gn.NET_BUILD_SINGLE_LAUNCH | gn.NET_BUILD_AUTOTUNE), ("resident", 0),
+                ("per-step", gn.NET_BUILD_PER_STEP)]
     wins = {name: 0 for name, _ in variants}
     largest = max(specs, key=lambda s: s.n_edges)
     largest_alone = {}
@@ -303,7 +303,7 @@ def bench_ensemble(args, torch, synth, gn):
             "value": len(specs) / seq_all * (steps / 10000.0),
             "unit": "networks per second (10,000-step runs)",
             "method": "each network on its own handle with the fastest of three settings (single-launch "
-                      "LDS-resident kernel autotuned, the two per-step kernels, the fused per-step kernel); "
+                      "kernel autotuned, the kernel resident over the chip, the two per-step kernels); "
                       "%d of %d networks timed and scaled" % (len(sample), len(specs)),
             "best_setting_counts": wins,
         },
@@ -311,14 +311,13 @@ def bench_ensemble(args, torch, synth, gn):
         "largest_network": {"n_vertices": largest.n, "n_edges": largest.n_edges},
         "speedup_vs_sequential": seq_all / wall,
         "edge_steps_per_s": E * steps / wall,
-        # The kernel pushes each spike along its out-edges from an LDS spike
-        # log (the in-edge stream is only the fallback of a step whose log
-        # overflowed), so it moves far fewer bytes than the edge-steps it
-        # covers: its bound is each workgroup's per-step latency (update,
-        # two barriers, the dependent loads of a push).  Its ceiling is the
-        # largest network alone on one workgroup with the same kernel.
+        # The kernel pushes each spike along its out-edges, so it moves far
+        # fewer bytes than the edge-steps it covers: its bound is each
+        # workgroup's per-step latency (update, a barrier, the dependent loads
+        # of a push).  Its ceiling is the largest network alone on one
+        # workgroup with the same kernel.
         "roofline": {
-            "bound": "latency", "kernel": "ensemble_kernel",
+            "bound": "latency", "kernel": "push_ensemble_kernel",
             "achieved": wall, "peak": largest_alone["single-launch"],
             "unit": "s per call of all steps (peak: the largest network alone, same kernel)",
             "frac": largest_alone["single-launch"] / wall,
@@ -553,14 +552,14 @@ def bench_testset(args, torch, synth, gn):
         # The slowest network alone bounds the launch (one workgroup each, per-step
         # latency: FP64 vertex arithmetic, barriers, the push of its spikes).
         "roofline": {
-            "bound": "latency", "kernel": "ensemble_kernel",
+            "bound": "latency", "kernel": "push_ensemble_kernel",
             "achieved": wall, "peak": sim_s / float(rtf.min()),
             "unit": "s per call of all steps (peak: the slowest network alone, same kernel)",
             "frac": sim_s / float(rtf.min()) / wall,
             "traffic": None,
             "pull_equivalent_GBps": BYTES_PER_EDGE * E * steps / (tm["ensemble_ms"] / 1e3) / 1e9,
             "note": "frac = the slowest network's own time over the whole launch's; the %.1f MB edge list is "
-                    "not streamed (spikes are pushed from LDS logs)" % (BYTES_PER_EDGE * E / 1e6),
+                    "not streamed (spikes are pushed along their out-edges)" % (BYTES_PER_EDGE * E / 1e6),
         },
         "paper_context": ("Section 3.4: on one Tesla C1060 its HH networks (dt 0.03 ms) ran in about real time "
                           "except the largest random ones (10-15x slower than real time); one 2.5 GHz Core2Duo "

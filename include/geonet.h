@@ -143,8 +143,9 @@ typedef struct {
        the weight its edge has when it arrives.  Needs the LIF vertex, one
        network per handle, n_ref >= 17 (the last 16 spike times of a vertex
        then cover the 255-step delay window) and weights that are multiples
-       of 2^-20 below 2048 after FP16 rounding; the per-step kernels are used
-       (build flags that select other kernels are ignored). */
+       of 2^-20 below 2048 after FP16 rounding; the per-step kernels or the
+       resident one are used (see NET_BUILD_PER_STEP; build flags that select
+       other kernels are ignored). */
     int32_t plastic;
     float stdp_alpha;             /* weight per ms */
     float stdp_beta;              /* 1/ms */

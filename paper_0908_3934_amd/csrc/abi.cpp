@@ -721,10 +721,13 @@ net_status step_loop(net* h, int64_t n_steps, const net_record* rec, hipStream_t
 }
 
 // Whether a call of n_steps goes to the resident kernel.  Its launch costs
-// about 20 us more than a step's kernels (6 to 13 us a step against 2 to 4):
-// calls below kResidentMinSteps stay with those, and where the ring of
-// arrivals has to be rebuilt first (about 100 us), calls below
-// kResidentMinRebuild.  A timing window times the step's kernels; a stream that
+// about 20 us more than a step's kernels: calls below kResidentMinSteps stay with
+// those (us per call of 4 and of 8 steps, per-step kernels and this one: 8,192
+// vertices 30 / 32 and 59 / 39, 65,536 45 / 40 and 89 / 49).  Where the ring of
+// arrivals has to be rebuilt first, which takes 15 to 40 us, calls below
+// kResidentMinRebuild do: a line that is safe but high (one per-step call and one
+// of 8, 16, 128 steps: 8,192 vertices 67, 126, 955 / 66, 79, 271; 65,536 101,
+// 190, 1,441 / 83, 100, 356).    A timing window times the step's kernels; a stream that
 // is being captured records them, whatever the call's length, and since its
 // replays move the state unseen, the handle then keeps to them.
 bool resident_route(net* h, int64_t n_steps, hipStream_t s) {

@@ -11,13 +11,14 @@
 // known as soon as step t has updated it, so at the start of a step all its
 // spikes stand in LDS, every wave takes an equal share of them whatever
 // vertices they belong to, and, since no push of step t touches slot t, a step
-// needs one barrier.  All sums are exact, so the order of the atomics changes
-// no bit.
+// needs one barrier.
 //
 // The slots hold integers: the weights of a network are multiples of its
-// smallest FP16 spacing, a power of two, and are added in that unit wherever a
-// row's sum fits 31 bits, which gives the very sum the FP32 additions would.
-// On gfx950 a 64-lane ds_add_f32 takes 80 ns of the CU's LDS, a ds_add_u32 to
+// smallest FP16 spacing, a power of two, and are added in that unit wherever
+// every row's sum of magnitudes fits 31 bits.  Such a sum is exact, so the
+// order of the atomics changes no bit, and where FP32 sums are exact too it is
+// the very same.  The other networks' slots hold floats, whose sums depend on
+// that order where a row is not exact in FP32 (NET_W_INEXACT).  On gfx950 a 64-lane ds_add_f32 takes 80 ns of the CU's LDS, a ds_add_u32 to
 // the same addresses 2.8 ns.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -33,6 +34,12 @@
 namespace geonet {
 namespace {
 
+// Groups up to which a wave pushes its own vertices' spikes (see push_run).  us
+// per step, shared and own, quiet networks of the 2-D kind: 64 vertices 0.38 /
+// 0.29, 256 0.42 / 0.34; 256 vertices of 26 out-edges each, 7 spikes a step 1.21
+// / 0.89.  With one vertex a lane it still is the faster form above this line
+// (320: 0.46 / 0.37, 512: 0.49 / 0.38, 512 with 15 spikes a step 1.57 / 1.35,
+// 1,024: 0.59 / 0.50).
 constexpr int kPushOwnGroups = 4;
 static_assert(kPushThreads / 64 * kPushMaxVpt <= kWordMaxGroups && kPushThreadsFp64 / 64 * kPushMaxVptFp64 <= kWordMaxGroups,
               "word_window is exact up to so many groups");
@@ -178,10 +185,10 @@ __device__ __forceinline__ void push_run(const const_args ka, const PushCtx& c, 
     const uint32_t my_w = word_window(static_cast<uint32_t>(lane), c.groups_inv);   // window and group of the lane's
     const uint32_t my_g = static_cast<uint32_t>(lane) - my_w * static_cast<uint32_t>(c.groups);   // first word
     // Small LIF networks of one window: a wave's own spikes, which it has in
-    // registers, straight away; nothing is shared (256 vertices, 1,000 steps:
-    // 568 us shared, 407 so).  In larger ones the spikes of a step gather in few
-    // waves, and where a lane has several vertices the second form's code alone
-    // costs 4 %.
+    // registers, straight away; nothing is shared.  In networks of the FP64 models
+    // the spikes of a step gather in few waves (densest Izhikevich one 7.6 us a
+    // step shared, above 9 so), and where a lane has several vertices the second
+    // form's code alone costs 4 %.
     constexpr bool kOwn = kModel == NET_MODEL_LIF && VPT == 1;
     const bool own = kOwn && c.own;
     uint64_t spk[VPT];                       // this wave's spikes of the step to come

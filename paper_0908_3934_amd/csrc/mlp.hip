@@ -1013,7 +1013,9 @@ int64_t mlp_ldt(int64_t B) { return (B + 7) / 8 * 8; }
 // Up to 16,384 rows 64-row tiles give a CU one workgroup, four waves that wait
 // for every stage and barrier together; 32-row tiles give it two.  An epoch of
 // 65,536 rows in batches of 16,384 with its launches: 594 us, with 32-row tiles
-// 543, and with the weight gradients' chunks below 478.
+// 543, and with the weight gradients' chunks below 478.  A training step, 64-row
+// and 32-row tiles: 8,192 rows 69 / 54 us, 16,384 (64 for each of 256 CUs) 74 /
+// 60, 24,576 82 / 80, 32,768 89 / 94, 65,536 155 / 160.
 constexpr int64_t kRows32 = 64 * 256;
 template <int kEpi>
 hipError_t gemm_rows(const GemmArgs& g, hipStream_t s) {
