@@ -126,27 +126,12 @@ void* dev_alloc(net* h, size_t bytes, hipStream_t s) {
         p = h->alloc(bytes, s, h->alloc_ctx);
     } else if (hipMalloc(&p, bytes) != hipSuccess) {
         p = nullptr;
-        (void)hipGetLastError();               // (the caller may go on without)
     }
     if (p) {
         h->blocks.push_back(p);
         h->device_bytes += static_cast<int64_t>(bytes);
     }
     return p;
-}
-
-// Gives back what was allocated after the first `blocks` blocks of `bytes`
-// bytes, for tables that a handle can do without.
-void release_since(net* h, size_t blocks, int64_t bytes, hipStream_t s) {
-    (void)hipStreamSynchronize(s);
-    for (size_t k = blocks; k < h->blocks.size(); ++k) {
-        if (h->release)
-            h->release(h->blocks[k], s, h->alloc_ctx);
-        else
-            (void)hipFree(h->blocks[k]);
-    }
-    h->blocks.resize(blocks);
-    h->device_bytes = bytes;
 }
 
 void release_all(net* h) {
@@ -318,9 +303,9 @@ bool weight_unit(const HostGraph& hg, int m, int* lg_out) {
     return most < (int64_t(1) << 31);
 }
 
-// Tables and LDS layout of the push ensemble kernel; false (and nothing kept)
-// where a network fits neither its registers nor its LDS, or there is no device
-// memory for them.  *st is set when an upload failed otherwise.
+// Tables and LDS layout of the push ensemble kernel; false (and nothing
+// uploaded) where a network fits neither its registers nor its LDS.  *st is
+// set when an upload failed.
 bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max, hipStream_t s, int* groups_max, size_t* lds_need,
                net_status* st) {
     const int n_nets = h->g.n_nets;
@@ -395,8 +380,6 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
         nets[m].inv_unit = fits ? std::ldexp(1.0f, -lg) : 0.0f;
     }
     if (edge.empty()) edge.push_back(0u);
-    const size_t had = h->blocks.size();
-    const int64_t held = h->device_bytes;
     // the costliest networks first: the workgroups that start last are short
     std::stable_sort(nets.begin(), nets.end(), [&](const PushNet& x, const PushNet& y) { return cost[x.net] > cost[y.net]; });
     EnsemblePlan& pl = h->plan;
@@ -413,23 +396,13 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
     if (noisy && 2 * n_nets <= n_cu && stride <= kNoiseMaxVertices) {
         const int32_t steps = static_cast<int32_t>(std::min<int64_t>(1024, kNoiseBytes / (stride * 8)));
         int32_t* dnn = nullptr;
-        double* noise = nullptr;
-        uint64_t* pulses = nullptr;
         *st = upload(h, &dnn, noise_nets, noise_nets.size(), s, "ensemble plan");
-        if (*st == NET_OK) *st = zeros(h, &noise, static_cast<size_t>(steps * stride), s, "noise");
-        if (*st == NET_OK) *st = zeros(h, &pulses, static_cast<size_t>(steps * (stride / 64)), s, "noise");
-        if (*st == NET_E_OOM) {
-            release_since(h, had, held, s);        // (drawn in the steps then)
-            *st = NET_OK;
-        } else if (*st != NET_OK) {
-            return false;
-        } else {
-            pl.noise = noise;
-            pl.noise_pulses = pulses;
-            pl.noise_nets = dnn;
-            pl.noise_stride = stride;
-            pl.noise_steps = steps;
-        }
+        if (*st == NET_OK) *st = zeros(h, &pl.noise, static_cast<size_t>(steps * stride), s, "noise");
+        if (*st == NET_OK) *st = zeros(h, &pl.noise_pulses, static_cast<size_t>(steps * (stride / 64)), s, "noise");
+        if (*st != NET_OK) return false;
+        pl.noise_nets = dnn;
+        pl.noise_stride = stride;
+        pl.noise_steps = steps;
     }
     PushNet* dn = nullptr;
     uint32_t *dof = nullptr, *ded = nullptr;
@@ -441,12 +414,6 @@ bool plan_push(net* h, const HostGraph& hg, int models, int n_cu, size_t lds_max
     if (*st == NET_OK) {
         const hipError_t e = hipStreamSynchronize(s);   // the host tables are freed below
         if (e != hipSuccess) *st = device_fail(h, e, "net_build: upload");
-    }
-    if (*st == NET_E_OOM) {
-        release_since(h, had, held, s);
-        pl = EnsemblePlan{};
-        *st = NET_OK;
-        return false;
     }
     if (*st != NET_OK) return false;
     pl.push_nets = dn;
@@ -516,8 +483,6 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
     if (hipMemGetInfo(&mem_free, &mem_total) != hipSuccess ||
         2 * (4 * n_off + 8 * static_cast<size_t>(hg.n_edges) + 4 * (ring_words + (r.plastic ? hg.e_slots : 0))) > mem_free)
         return NET_OK;
-    const size_t had = h->blocks.size();
-    const int64_t held = h->device_bytes;
     uint32_t *doff = nullptr, *sums = nullptr;
     uint2* dedge = nullptr;
     net_status st = zeros(h, &doff, n_off, s, "resident edges");
@@ -536,17 +501,13 @@ net_status plan_resident(net* h, const HostGraph& hg, hipStream_t s) {
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) st = device_fail(h, e, "net_build: resident edges");
     }
-    if (st == NET_OK && (hipHostMalloc(reinterpret_cast<void**>(&r.fail), sizeof(uint32_t), hipHostMallocMapped) != hipSuccess ||
-                         hipHostGetDevicePointer(reinterpret_cast<void**>(&r.fail_dev), r.fail, 0) != hipSuccess)) {
+    if (st != NET_OK) return st;
+    if (hipHostMalloc(reinterpret_cast<void**>(&r.fail), sizeof(uint32_t), hipHostMallocMapped) != hipSuccess ||
+        hipHostGetDevicePointer(reinterpret_cast<void**>(&r.fail_dev), r.fail, 0) != hipSuccess) {
         (void)hipGetLastError();
         if (r.fail) (void)hipHostFree(r.fail);
-        st = NET_E_OOM;
-    }
-    if (st == NET_E_OOM) {                              // (the per-step kernels then)
-        release_since(h, had, held, s);
         return NET_OK;
     }
-    if (st != NET_OK) return st;
     *r.fail = 0u;
     r.off = doff;
     r.edge = dedge;
